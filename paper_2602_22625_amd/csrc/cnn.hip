@@ -20,6 +20,7 @@
 
 #include <algorithm>
 
+#include "cnn_kernels.h"
 #include "dbmp_cnn.h"
 
 namespace dbmp_cnn {
@@ -608,6 +609,9 @@ int dbmp_cnn_conv_forward(void *stream, const uint16_t *x, int B, int H, int W, 
     if (!x || !w || (!y && !y32) || B < 1 || H < 2 || W < 2 || (H & 1) || (W & 1) ||
         Cin < 8 || (Cin & 7) || Cout < 1)
         return DBMP_CNN_EINVAL;
+    hipError_t e;
+    if (conv_forward_direct((hipStream_t)stream, x, B, H, W, Cin, w, bias, Cout, relu, y, y32, &e))
+        return status(e);
     const int OH = H / 2, OW = W / 2, M = B * OH * OW, K = 9 * Cin;
     LIm2col la{x, H, W, Cin, OH, OW, M, K};
     LPlain lb{w, K, Cout, K};
@@ -622,6 +626,9 @@ int dbmp_cnn_conv_backward_data(void *stream, const uint16_t *dz, int B, int H, 
     if (!dz || !wt || !dx || B < 1 || H < 2 || W < 2 || (H & 1) || (W & 1) || Cin < 1 ||
         Cout < 8 || (Cout & 7) || (Cin & 7))
         return DBMP_CNN_EINVAL;
+    hipError_t e;
+    if (conv_backward_data_direct((hipStream_t)stream, dz, B, H, W, Cin, wt, Cout, mask, dx, &e))
+        return status(e);
     const int OH = H / 2, OW = W / 2, M4 = B * OH * OW;
     // one launch over the four parity classes (the kernel sets each class's taps and K)
     const Phase none{0, 0, 0, 0, 0, 0};
