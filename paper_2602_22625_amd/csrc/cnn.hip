@@ -647,11 +647,12 @@ int dbmp_cnn_conv_backward_weight(void *stream, const uint16_t *x, const uint16_
     if (!x || !dz || !dw || B < 1 || H < 2 || W < 2 || (H & 1) || (W & 1) || Cin < 1 ||
         Cout < 1)
         return DBMP_CNN_EINVAL;
+    hipStream_t st = (hipStream_t)stream;
+    hipError_t e;
+    if (conv_backward_weight_direct(st, x, dz, B, H, W, Cin, Cout, dw, db, &e)) return status(e);
     const int OH = H / 2, OW = W / 2, P = B * OH * OW, N = 9 * Cin;
     EAdd ep{dw, N};
-    hipStream_t st = (hipStream_t)stream;
     const int sp = splits_for(Cout, N, P);
-    hipError_t e;
     // A(oc, p) = dz[p][oc], B(n, p) = patch value: both read across K = output pixels, their
     // rows (channels) contiguous in NHWC, so 16-byte loads where the channel counts allow
     if (Cout % 8 == 0 && Cin % 8 == 0 && ((uintptr_t)dz & 15) == 0 && ((uintptr_t)x & 15) == 0)

@@ -1,4 +1,4 @@
-// Launchers of the convolution kernels in conv.hip, used by the layer entry points of cnn.hip.
+// Launchers of the convolution kernels in conv.hip and wgrad.hip, used by the layer entry points of cnn.hip.
 // Each returns false, with nothing launched, for a layer it has no build for (the entry point
 // then takes the general gather product); otherwise it launches and leaves the status in *err.
 #pragma once
@@ -17,5 +17,10 @@ bool conv_forward_direct(hipStream_t st, const uint16_t *x, int B, int H, int W,
 bool conv_backward_data_direct(hipStream_t st, const uint16_t *dz, int B, int H, int W, int Cin,
                                const uint16_t *wt, int Cout, const uint16_t *mask, uint16_t *dx,
                                hipError_t *err);
+
+// dw += dz^T patches(x), db += column sums of dz (db may be null)
+bool conv_backward_weight_direct(hipStream_t st, const uint16_t *x, const uint16_t *dz, int B,
+                                 int H, int W, int Cin, int Cout, float *dw, float *db,
+                                 hipError_t *err);
 
 }  // namespace dbmp_cnn

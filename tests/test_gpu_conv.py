@@ -60,6 +60,31 @@ def test_forward_and_input_gradient_exact(shape):
         assert np.array_equal(dx.float().cpu().numpy(), want)
 
 
+# (B, H, W, Cin, Cout): output rows of 8 k and of 4 pixels, pixel counts that leave the last 32-pixel
+# step partly empty, one step, several pixel splits, each channel tile; the last two take the general
+# product (an output row of 9 pixels, 24 channels)
+WSHAPES = [(1, 2, 16, 8, 32), (3, 6, 16, 8, 64), (1, 2, 16, 32, 64), (3, 10, 8, 32, 32),
+           (5, 6, 24, 64, 96), (2, 16, 8, 128, 64), (1, 8, 8, 256, 256), (4, 64, 64, 32, 64),
+           (4, 64, 64, 8, 32), (1, 4, 18, 32, 64), (1, 4, 16, 32, 24)]
+
+
+@pytest.mark.parametrize("shape", WSHAPES)
+def test_weight_and_bias_gradient_exact(shape):
+    B, H, W, Ci, Co = shape
+    g = np.random.default_rng(sum(shape))
+    x, dz = dyadic(g, (B, H, W, Ci), 4, 4), dyadic(g, (B, H // 2, W // 2, Co), 4, 16)
+    rw, rb = co.conv_backward_weight(x, dz)
+    for with_bias in (True, False):
+        dw = torch.full((Co, 3, 3, Ci), 0.5, device="cuda")
+        db = torch.full((Co,), -0.25, device="cuda") if with_bias else None
+        capi.dbmp_cnn_conv_backward_weight(capi.stream_handle(), bf(x), bf(dz), B, H, W, Ci, Co, dw,
+                                           db)
+        torch.cuda.synchronize()
+        assert np.array_equal(dw.cpu().numpy(), (rw + 0.5).astype(np.float32))
+        if with_bias:
+            assert np.array_equal(db.cpu().numpy(), (rb - 0.25).astype(np.float32))
+
+
 @pytest.mark.parametrize("B,S,Ci,Co", [(70, 32, 32, 64), (33, 32, 32, 64), (9, 64, 64, 32)])
 def test_wave_tiles_agree(B, S, Ci, Co):
     """Batches that take the larger wave tiles equal the same images one at a time (the smallest
