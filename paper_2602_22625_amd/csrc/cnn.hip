@@ -471,7 +471,9 @@ __global__ void __launch_bounds__(256) k_colsum(const u16 *__restrict__ z, int M
 static hipError_t colsum(hipStream_t st, const u16 *dz, int M, int N, float *db)
 {
     if (N % 8 == 0 && N <= 2048 && ((uintptr_t)dz & 15) == 0) {
-        const int rows = 2048;
+        // up to 256 workgroups of at least 8 passes over their rows (2,048 rows per workgroup left
+        // the head's 1,024 rows to one: 36 us for N = 512, 6 us now)
+        const int rows = std::max(8 * 4 * (256 / (N >> 3)), (M + 255) / 256);
         k_colsum8<<<(M + rows - 1) / rows, 256, 0, st>>>(dz, M, N, rows, db);
     } else {
         const int rows = 4096;
@@ -521,6 +523,11 @@ struct Col8 {
     float v[8];
 };
 
+// A workgroup adds its share of the loss with one atomic; they all meet on one address at about
+// 14 ns each (2,048 workgroups of one value per thread: 29 us for 524,288 values), so at most
+// LOSS_BLOCKS of them stride over the values.
+constexpr int LOSS_BLOCKS = 256;
+
 __global__ void __launch_bounds__(256) k_param_loss(const float *__restrict__ pred,
                                                     const float *__restrict__ tgt,
                                                     const float *__restrict__ w, long long n,
@@ -528,25 +535,29 @@ __global__ void __launch_bounds__(256) k_param_loss(const float *__restrict__ pr
                                                     Col8 xs, u16 *__restrict__ dpred,
                                                     float *__restrict__ loss)
 {
-    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const int q = threadIdx.x & 7;  // the value's column: the stride is a multiple of 8
+    const float wq = tgt ? w[q] : 0.f;
+    float xq = xs.v[0];
+#pragma unroll
+    for (int k = 1; k < 8; ++k) xq = q == k ? xs.v[k] : xq;
     float l = 0.f;
-    if (i < n) {
-        const int q = (int)(i & 7);
+    for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n;
+         i += (long long)gridDim.x * 256) {
         float g = 0.f;
         if (tgt) {
             const float d = pred[i] - tgt[i];
             if (q == 3) {
                 float sn, cs;
                 __sincosf(d, &sn, &cs);
-                l = w[q] * (1.f - cs);
-                g = w[q] * sn;
+                l += wq * (1.f - cs);
+                g = wq * sn;
             } else {
-                l = w[q] * d * d;
-                g = 2.f * w[q] * d;
+                l += wq * d * d;
+                g = 2.f * wq * d;
             }
         }
         g *= scale;
-        if (extra) g = fmaf(extra[i], xs.v[q], g);
+        if (extra) g = fmaf(extra[i], xq, g);
         dpred[i] = f2bf(g);
     }
     __shared__ float part[256];
@@ -730,7 +741,8 @@ int dbmp_cnn_param_loss(void *stream, const float *pred, const float *target,
     Col8 xs{};
     if (extra)
         for (int q = 0; q < 8; ++q) xs.v[q] = extra_scale8[q];
-    k_param_loss<<<(unsigned)((n + 255) / 256), 256, 0, (hipStream_t)stream>>>(
+    const long long blocks = std::min<long long>((n + 255) / 256, LOSS_BLOCKS);
+    k_param_loss<<<(unsigned)blocks, 256, 0, (hipStream_t)stream>>>(
         pred, target, weights8, n, scale, extra, xs, dpred, loss);
     return status(hipGetLastError());
 }
