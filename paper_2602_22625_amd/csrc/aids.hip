@@ -8,16 +8,20 @@
 #include "diffbmp.h"
 
 #include <limits.h>
-#include <algorithm>
 #include <math.h>
+
+#include <algorithm>
 
 namespace dbmp {
 namespace {
 
 // ------------------------------------------------------------------------------------------
 // Gaussian blur (Sec. 3.2.1): a band of output rows per workgroup. The band's input rows plus
-// r rows above and below are staged in LDS (as float32), blurred along x into a second LDS
-// buffer, then along y into the output: each input texel is read from HBM once per band.
+// r rows above and below are staged in LDS (as float32, between r columns of zeros), blurred along
+// x into a second LDS buffer, then along y into the output. Waves take rows, lanes columns: no
+// division. Bands are short where that fills the chip (a 64 x 128 x 128 atlas, 16 rows: 512
+// workgroups): bands as tall as LDS holds left one workgroup per compute unit, and each of its
+// threads 24 pixels of dependent LDS reads: 33 us for a 64 x 128 x 128 bfloat16 atlas, 10 us now.
 // ------------------------------------------------------------------------------------------
 constexpr int BLUR_RMAX = 16;
 constexpr int BLUR_LDS_BYTES = 48 * 1024;
@@ -41,47 +45,55 @@ template <> __device__ __forceinline__ _Float16 from_f32<_Float16>(float v)
     return (_Float16)v;  // round to nearest even
 }
 
-template <typename TexT>
+// RAD > 0: the radius at compile time (3 is sigma = 1, the method's), so that a pixel's LDS reads
+// are all in flight; 0: t.r.
+template <typename TexT, int RAD>
 __global__ void __launch_bounds__(256)
 k_blur(const TexT *__restrict__ in, TexT *__restrict__ out, int Hb, int Wb, int band, BlurTaps t)
 {
     extern __shared__ float sh[];
-    const int b = blockIdx.y, y0 = blockIdx.x * band, r = t.r, rows = band + 2 * r;
-    float *raw = sh;               // rows y0 - r .. y0 + band + r - 1 (zero outside the bitmap)
-    float *hor = sh + rows * Wb;   // the same rows blurred along x
+    const int r = RAD ? RAD : t.r;
+    const int b = blockIdx.y, y0 = blockIdx.x * band, rows = band + 2 * r;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, pitch = Wb + 2 * r;
+    float *raw = sh;                  // rows y0 - r .. y0 + band + r - 1 (zero outside the bitmap)
+    float *hor = sh + rows * pitch;   // the same rows blurred along x
     const TexT *src = in + (size_t)b * Hb * Wb;
-    for (int i = threadIdx.x; i < rows * Wb; i += 256) {
-        const int yy = y0 - r + i / Wb, xx = i - (i / Wb) * Wb;
-        raw[i] = (yy >= 0 && yy < Hb) ? texel<TexT>(src[(size_t)yy * Wb + xx]) : 0.f;
+    for (int y = wave; y < rows; y += 4) {
+        const int yy = y0 - r + y;
+        const bool in_y = yy >= 0 && yy < Hb;
+        for (int x = lane; x < pitch; x += 64) {
+            const int xx = x - r;
+            raw[y * pitch + x] =
+                in_y && xx >= 0 && xx < Wb ? texel<TexT>(src[(size_t)yy * Wb + xx]) : 0.f;
+        }
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < rows * Wb; i += 256) {
-        const int yy = i / Wb, xx = i - yy * Wb;
-        float acc = 0.f;
-        for (int d = -r; d <= r; ++d) {
-            const int x2 = xx + d;
-            if (x2 >= 0 && x2 < Wb) acc = fmaf(t.w[d + r], raw[yy * Wb + x2], acc);
+    for (int y = wave; y < rows; y += 4)
+        for (int x = lane; x < Wb; x += 64) {
+            const float *p = raw + y * pitch + x;
+            float acc = 0.f;
+            for (int d = 0; d <= 2 * r; ++d) acc = fmaf(t.w[d], p[d], acc);
+            hor[y * Wb + x] = acc;
         }
-        hor[i] = acc;
-    }
     __syncthreads();
     TexT *dst = out + (size_t)b * Hb * Wb;
-    for (int i = threadIdx.x; i < band * Wb; i += 256) {
-        const int yl = i / Wb, xx = i - yl * Wb, yy = y0 + yl;
-        if (yy >= Hb) continue;
-        float acc = 0.f;
-        for (int d = -r; d <= r; ++d) acc = fmaf(t.w[d + r], hor[(yl + r + d) * Wb + xx], acc);
-        dst[(size_t)yy * Wb + xx] = from_f32<TexT>(acc);
-    }
+    for (int y = wave; y < min(band, Hb - y0); y += 4)
+        for (int x = lane; x < Wb; x += 64) {
+            const float *p = hor + y * Wb + x;
+            float acc = 0.f;
+            for (int d = 0; d <= 2 * r; ++d) acc = fmaf(t.w[d], p[d * Wb], acc);
+            dst[(size_t)(y0 + y) * Wb + x] = from_f32<TexT>(acc);
+        }
 }
 
 // ------------------------------------------------------------------------------------------
 // Structure-aware initialisation (Sec. 3.2.2)
 // ------------------------------------------------------------------------------------------
-constexpr int LV_T = 16;      // output pixels per workgroup edge
-constexpr int LV_HMAX = 7;    // largest window half-width (15 x 15)
-constexpr int SCAN_ITEMS = 8; // int64 weights per thread of a scan block
-constexpr int SCAN_BLOCK = 256 * SCAN_ITEMS;
+constexpr int LV_W = 64;        // output columns per workgroup
+constexpr int LV_HMAX = 7;      // largest window half-width (15 x 15)
+constexpr int NLV_BLOCK = 4096; // pixels per workgroup of k_nlv
+constexpr int NLV_GROUP = 64;   // pixels whose sampling weights are summed to one entry
+constexpr int BSUM_LDS = 2048;  // block totals the sampler scans in LDS
 
 // Ordering of non-negative doubles = ordering of their bit patterns as unsigned integers.
 __device__ __forceinline__ unsigned long long dbits(double x)
@@ -89,56 +101,114 @@ __device__ __forceinline__ unsigned long long dbits(double x)
     return (unsigned long long)__double_as_longlong(x);
 }
 
-// LV of a 16 x 16 pixel block: the (16 + 2h)^2 window of the three channels is staged in LDS;
-// each lane sums its pixel's window (only pixels inside the image) in float64.
+// a / n for an integer n, given inv = 1 / n rounded to nearest: one Newton step on the quotient,
+// which is then a / n rounded to nearest (so that a flat region's variance is exactly 0, which a
+// product with inv would miss).
+__device__ __forceinline__ double div_n(double a, double n, double inv)
+{
+    const double q = a * inv;
+    return fma(fma(-q, n, a), inv, q);
+}
+
+// Sum of N values, pairwise.
+template <int N, typename At>
+__device__ __forceinline__ double tree_sum(At at, int i0 = 0)
+{
+    if constexpr (N == 0) return 0.0;
+    else if constexpr (N == 1) return at(i0);
+    else {
+        constexpr int K = N > 4 ? 4 : N > 2 ? 2 : 1;
+        return tree_sum<K>(at, i0) + tree_sum<N - K>(at, i0 + K);
+    }
+}
+
+// The local variance (float64) over the (2 h + 1)^2 window clipped to the image, 64 columns by 4 R
+// rows per workgroup. Per channel: each row's window sums of values and squares along x into LDS
+// (values straight from memory: a window's loads hit the same lines), then each wave adds up
+// 2 h + 1 rows of them for its R rows of outputs: about 45 float64 operations per pixel and channel
+// for a 7 x 7 window (R = 8), where summing the window afresh took 98 and as many conversions:
+// 67 us at 2048 x 2048, 176 before. Bound by latency (three waves per SIMD beside the outputs'
+// registers; the operations alone would take 27 us). Keeping the row sums in registers instead
+// took 62 us with strips of 4 rows, 79 with 8, and spilled for the larger windows.
+template <int HW, int R>
 __global__ void __launch_bounds__(256)
-k_local_var(const float *__restrict__ img, int H, int W, int h, double *__restrict__ lv,
+k_local_var(const float *__restrict__ img, int H, int W, double *__restrict__ lv,
             unsigned long long *__restrict__ bmm)
 {
-    constexpr int S = LV_T + 2 * LV_HMAX;
-    __shared__ float s[3][S][S];
-    const int bx = blockIdx.x * LV_T, by = blockIdx.y * LV_T, e = LV_T + 2 * h;
+    constexpr int WIN = 2 * HW + 1, ROWS = 4 * R + 2 * HW;
+    __shared__ double s1[ROWS][LV_W], s2[ROWS][LV_W];
+    __shared__ double s_inv[WIN * WIN + 1];  // reciprocals of the window's pixel counts
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (threadIdx.x <= WIN * WIN) s_inv[threadIdx.x] = 1.0 / max((int)threadIdx.x, 1);
+    const int bx = blockIdx.x * LV_W, by = blockIdx.y * 4 * R, x = bx + lane;
     const size_t plane = (size_t)H * W;
-    for (int i = threadIdx.x; i < 3 * e * e; i += 256) {
-        const int c = i / (e * e), q = i - c * e * e, yy = by - h + q / e, xx = bx - h + q % e;
-        s[c][q / e][q % e] = (yy >= 0 && yy < H && xx >= 0 && xx < W)
-                                 ? img[c * plane + (size_t)yy * W + xx] : 0.f;
-    }
-    __syncthreads();
-    const int lx = threadIdx.x % LV_T, ly = threadIdx.x / LV_T;
-    const int x = bx + lx, y = by + ly;
-    double v = 0.0;
-    const bool ok = x < W && y < H;
-    if (ok) {
-        const int x0 = max(x - h, 0) - (bx - h), x1 = min(x + h, W - 1) - (bx - h);
-        const int y0 = max(y - h, 0) - (by - h), y1 = min(y + h, H - 1) - (by - h);
-        const double n = (double)((x1 - x0 + 1) * (y1 - y0 + 1));
-        for (int c = 0; c < 3; ++c) {
-            double s1 = 0.0, s2 = 0.0;
-            for (int yy = y0; yy <= y1; ++yy)
-                for (int xx = x0; xx <= x1; ++xx) {
-                    const double a = s[c][yy][xx];
-                    s1 += a;
-                    s2 = fma(a, a, s2);
+    const bool inside = bx >= HW && bx + LV_W + HW <= W;  // no lane's window leaves the image in x
+    const int nx = max(min(x + HW, W - 1) - max(x - HW, 0) + 1, 1);
+    double v[R];
+#pragma unroll
+    for (int o = 0; o < R; ++o) v[o] = 0.0;
+    for (int c = 0; c < 3; ++c) {
+        if (c) __syncthreads();  // the previous channel's sums are read
+#pragma unroll 2
+        for (int q = wave; q < ROWS; q += 4) {
+            const int y = by - HW + q;
+            float f[WIN];
+#pragma unroll
+            for (int k = 0; k < WIN; ++k) f[k] = 0.f;
+            if (y >= 0 && y < H) {
+                const float *row = img + c * plane + (size_t)y * W;
+#pragma unroll
+                for (int k = 0; k < WIN; ++k) {
+                    const int xx = x + k - HW;
+                    if (inside) f[k] = row[xx];
+                    else if (xx >= 0 && xx < W) f[k] = row[xx];
                 }
-            const double m = s1 / n;
-            v += s2 / n - m * m;
+            }
+            s1[q][lane] = tree_sum<WIN>([&](int k) { return (double)f[k]; });
+            double sq = (double)f[0] * (double)f[0];  // squares of float32 values are exact
+#pragma unroll
+            for (int k = 1; k < WIN; ++k) sq = fma((double)f[k], (double)f[k], sq);
+            s2[q][lane] = sq;
         }
-        v = fmax(v / 3.0, 0.0);  // the one-pass form can round a zero variance below zero
-        lv[(size_t)y * W + x] = v;
+        __syncthreads();
+        double a1[R + 2 * HW], a2[R + 2 * HW];
+#pragma unroll
+        for (int k = 0; k < R + 2 * HW; ++k) {
+            a1[k] = s1[wave * R + k][lane];
+            a2[k] = s2[wave * R + k][lane];
+        }
+#pragma unroll
+        for (int o = 0; o < R; ++o) {
+            const int y = by + wave * R + o;
+            const int ni = nx * max(min(y + HW, H - 1) - max(y - HW, 0) + 1, 1);
+            const double n = ni, inv = s_inv[ni];
+            const double m = div_n(tree_sum<WIN>([&](int k) { return a1[o + k]; }), n, inv);
+            v[o] += div_n(tree_sum<WIN>([&](int k) { return a2[o + k]; }), n, inv) - m * m;
+        }
+    }
+    unsigned long long lo = 0x7ff0000000000000ull, hi = 0ull;
+#pragma unroll
+    for (int o = 0; o < R; ++o) {
+        const int y = by + wave * R + o;
+        if (x >= W || y >= H) continue;
+        // the one-pass form can round a zero variance below zero
+        const double d = fmax(div_n(v[o], 3.0, 1.0 / 3.0), 0.0);
+        lv[(size_t)y * W + x] = d;
+        const unsigned long long u = dbits(d);
+        lo = u < lo ? u : lo;
+        hi = u > hi ? u : hi;
     }
     // the block's min / max of the map (bit patterns of non-negative doubles), written to its
-    // own slot (k_lv_minmax reduces the slots: no same-address atomics across the grid)
-    unsigned long long lo = ok ? dbits(v) : 0x7ff0000000000000ull, hi = ok ? dbits(v) : 0ull;
+    // own slot (no same-address atomics across the grid)
     for (int o = 32; o > 0; o >>= 1) {
         const unsigned long long a = __shfl_xor(lo, o), b = __shfl_xor(hi, o);
         lo = a < lo ? a : lo;
         hi = b > hi ? b : hi;
     }
     __shared__ unsigned long long s_lo[4], s_hi[4];
-    if ((threadIdx.x & 63) == 0) {
-        s_lo[threadIdx.x >> 6] = lo;
-        s_hi[threadIdx.x >> 6] = hi;
+    if (lane == 0) {
+        s_lo[wave] = lo;
+        s_hi[wave] = hi;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -183,24 +253,87 @@ k_lv_minmax(const unsigned long long *__restrict__ bmm, int nblocks,
     }
 }
 
-// NLV (float32, the caller's map) and the integer sampling weights computed from it.
-__global__ void __launch_bounds__(256)
-k_nlv(const double *__restrict__ lv, long long n, const unsigned long long *__restrict__ minmax,
-      double base, float *__restrict__ nlv_out, long long *__restrict__ w)
+// The integer sampling weight of a pixel from its NLV (below 2^24 + 1).
+__device__ __forceinline__ uint32_t sample_weight(float nf, double base)
 {
-    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    const double lo = __longlong_as_double((long long)minmax[0]);
-    const double hi = __longlong_as_double((long long)minmax[1]);
-    const double q = hi > lo ? (lv[i] - lo) / (hi - lo) : 0.0;
-    const float nf = (float)q;
-    nlv_out[i] = nf;
     const double wd = base + (1.0 - base) * (double)nf;  // built without contraction
-    w[i] = (long long)floor(wd * 16777216.0);
+    return (uint32_t)floor(wd * 16777216.0);
 }
 
-// Inclusive int64 scan in three launches: per-block scans (2,048 values, 8 per lane) that also
-// leave each block's total; a one-workgroup scan of the totals; the offsets added back.
+// NLV (float32, the caller's map) and the sums of the sampling weights computed from it, in two
+// levels: inclusive sums over the workgroup's groups of 64 pixels, and its total. The sampler
+// recomputes a group's weights from the map: writing and scanning one int64 per pixel instead
+// moved 136 MB more at 2048 x 2048 (59 us for this kernel and the scan's three, 15 us now). Every
+// workgroup reduces the map's min / max from the nslots of k_local_var (or of k_lv_minmax) itself.
+__global__ void __launch_bounds__(256)
+k_nlv(const double *__restrict__ lv, long long n, const unsigned long long *__restrict__ bmm,
+      int nslots, double base, float *__restrict__ nlv_out, long long *__restrict__ gsum,
+      long long *__restrict__ bsum)
+{
+    __shared__ unsigned long long s_lo[4], s_hi[4];
+    __shared__ uint32_t s_g[NLV_BLOCK / NLV_GROUP];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const long long p0 = (long long)blockIdx.x * NLV_BLOCK;
+    double d[4][4];  // this thread's pixels, requested before the reduction below
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const long long p = p0 + k * 1024 + threadIdx.x * 4;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) d[k][j] = p + j < n ? lv[p + j] : 0.0;
+    }
+    unsigned long long lo = 0x7ff0000000000000ull, hi = 0ull;
+    for (int b = threadIdx.x; b < nslots; b += 256) {
+        lo = bmm[2 * b] < lo ? bmm[2 * b] : lo;
+        hi = bmm[2 * b + 1] > hi ? bmm[2 * b + 1] : hi;
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        const unsigned long long a = __shfl_xor(lo, o), b = __shfl_xor(hi, o);
+        lo = a < lo ? a : lo;
+        hi = b > hi ? b : hi;
+    }
+    if (lane == 0) {
+        s_lo[wave] = lo;
+        s_hi[wave] = hi;
+    }
+    __syncthreads();
+    for (int w = 0; w < 4; ++w) {
+        lo = s_lo[w] < lo ? s_lo[w] : lo;
+        hi = s_hi[w] > hi ? s_hi[w] : hi;
+    }
+    const double dlo = __longlong_as_double((long long)lo);
+    const double dhi = __longlong_as_double((long long)hi);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const long long p = p0 + k * 1024 + threadIdx.x * 4;
+        float f[4];
+        uint32_t w = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const double q = dhi > dlo ? (d[k][j] - dlo) / (dhi - dlo) : 0.0;
+            f[j] = (float)q;
+            if (p + j < n) w += sample_weight(f[j], base);
+        }
+        if (p + 3 < n && ((uintptr_t)nlv_out & 15) == 0) {
+            *reinterpret_cast<float4 *>(nlv_out + p) = make_float4(f[0], f[1], f[2], f[3]);
+        } else {
+            for (int j = 0; j < 4; ++j)
+                if (p + j < n) nlv_out[p + j] = f[j];
+        }
+        for (int o = 8; o > 0; o >>= 1) w += __shfl_xor(w, o);  // 16 lanes: 64 pixels, below 2^31
+        if ((lane & 15) == 0) s_g[k * 16 + (threadIdx.x >> 4)] = w;
+    }
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        long long x = s_g[threadIdx.x];
+        for (int o = 1; o < 64; o <<= 1) {
+            const long long y = __shfl_up(x, o, 64);
+            if (lane >= o) x += y;
+        }
+        gsum[(size_t)blockIdx.x * 64 + threadIdx.x] = x;
+        if (threadIdx.x == 63) bsum[blockIdx.x] = x;
+    }
+}
+
 __device__ __forceinline__ long long wave_incl_scan(long long x, int lane)
 {
     for (int o = 1; o < 64; o <<= 1) {
@@ -210,31 +343,8 @@ __device__ __forceinline__ long long wave_incl_scan(long long x, int lane)
     return x;
 }
 
-__global__ void __launch_bounds__(256)
-k_scan_blocks(long long *__restrict__ w, long long n, long long *__restrict__ bsum)
-{
-    __shared__ long long wsum[4];
-    const long long base = (long long)blockIdx.x * SCAN_BLOCK + threadIdx.x * SCAN_ITEMS;
-    long long v[SCAN_ITEMS];
-    long long run = 0;
-#pragma unroll
-    for (int k = 0; k < SCAN_ITEMS; ++k) {
-        v[k] = base + k < n ? w[base + k] : 0;
-        run += v[k];
-        v[k] = run;
-    }
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const long long incl = wave_incl_scan(run, lane);
-    if (lane == 63) wsum[wave] = incl;
-    __syncthreads();
-    long long off = incl - run;
-    for (int q = 0; q < wave; ++q) off += wsum[q];
-#pragma unroll
-    for (int k = 0; k < SCAN_ITEMS; ++k)
-        if (base + k < n) w[base + k] = v[k] + off;
-    if (threadIdx.x == 255) bsum[blockIdx.x] = off + run;
-}
-
+// Inclusive scan of the block totals in place, one workgroup (more totals than the sampler scans
+// itself).
 __global__ void __launch_bounds__(1024) k_scan_sums(long long *__restrict__ bsum, int nb)
 {
     __shared__ long long wsum[16];
@@ -257,31 +367,84 @@ __global__ void __launch_bounds__(1024) k_scan_sums(long long *__restrict__ bsum
     }
 }
 
+// One primitive per lane: inverse-CDF draw of its pixel, then its parameter row. The pixel is found
+// from the block totals (scanned in LDS, or already scanned in memory: SCANNED), the block's sums
+// over groups of 64 pixels, and the group's weights (65,536 draws from 2048 x 2048: 13 us, 17 with
+// 22 dependent steps through the whole cumulative sum).
+template <bool SCANNED>
 __global__ void __launch_bounds__(256)
-k_scan_add(long long *__restrict__ w, long long n, const long long *__restrict__ bsum)
+k_sa_sample(const long long *__restrict__ gsum, const long long *__restrict__ bsum, int nb,
+            long long n, double base, const float *__restrict__ nlv, const float *__restrict__ img,
+            int H, int W, const float *__restrict__ u_pos, const float *__restrict__ u_theta,
+            const float *__restrict__ z, int N, double s_min, double s_max, double nu_init,
+            double sigma_c, float *__restrict__ params)
 {
-    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (i < n && i >= SCAN_BLOCK) w[i] += bsum[i / SCAN_BLOCK - 1];
-}
-
-// One primitive per lane: inverse-CDF draw of its pixel, then its parameter row.
-__global__ void __launch_bounds__(256)
-k_sa_sample(const long long *__restrict__ cdf, long long n, const float *__restrict__ nlv,
-            const float *__restrict__ img, int H, int W, const float *__restrict__ u_pos,
-            const float *__restrict__ u_theta, const float *__restrict__ z, int N, double s_min,
-            double s_max, double nu_init, double sigma_c, float *__restrict__ params)
-{
+    __shared__ long long s_b[SCANNED ? 1 : BSUM_LDS];
+    __shared__ long long s_w[4];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if constexpr (!SCANNED) {  // inclusive sums of the totals
+        constexpr int PER = BSUM_LDS / 256;
+        long long v[PER], run = 0;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const int b = threadIdx.x * PER + k;
+            v[k] = b < nb ? bsum[b] : 0;
+        }
+#pragma unroll
+        for (int k = 0; k < PER; ++k) v[k] = run += v[k];
+        const long long incl = wave_incl_scan(run, lane);
+        if (lane == 63) s_w[wave] = incl;
+        __syncthreads();
+        long long off = incl - run;
+        for (int w = 0; w < wave; ++w) off += s_w[w];
+#pragma unroll
+        for (int k = 0; k < PER; ++k) s_b[threadIdx.x * PER + k] = v[k] + off;
+        __syncthreads();
+    }
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= N) return;
-    const long long total = cdf[n - 1];
+    auto total_to = [&](int b) { return SCANNED ? bsum[b] : s_b[b]; };
+    const long long total = total_to(nb - 1);
     long long t = (long long)floor((double)u_pos[i] * (double)total);
     if (t >= total) t = total - 1;
-    long long lo = 0, hi = n - 1;  // first p with cdf[p] > t
+    int lo = 0, hi = nb - 1;  // first block whose inclusive total exceeds t
     while (lo < hi) {
-        const long long mid = (lo + hi) >> 1;
-        if (cdf[mid] > t) hi = mid; else lo = mid + 1;
+        const int mid = (lo + hi) >> 1;
+        if (total_to(mid) > t) hi = mid; else lo = mid + 1;
     }
-    const int p = (int)lo, x = p % W, y = p / W;
+    const int blk = lo;
+    t -= blk ? total_to(blk - 1) : 0;
+    // first group whose inclusive sum exceeds t: the entries at most t are counted, eight at a
+    // time (independent loads)
+    const long long *gs = gsum + (size_t)blk * 64;
+    int gr = 0;
+#pragma unroll
+    for (int k = 0; k < 7; ++k) gr += gs[8 * k + 7] <= t ? 8 : 0;
+    const int g8 = gr;
+#pragma unroll
+    for (int k = 0; k < 7; ++k) gr += gs[g8 + k] <= t ? 1 : 0;
+    t -= gr ? gs[gr - 1] : 0;
+    // first pixel of the group whose cumulative weight exceeds t
+    const long long p0 = (long long)blk * NLV_BLOCK + gr * NLV_GROUP;
+    long long run = 0;
+    int at = 0;
+    if (p0 + NLV_GROUP <= n && ((uintptr_t)nlv & 15) == 0) {
+        float4 q[NLV_GROUP / 4];
+#pragma unroll
+        for (int k = 0; k < NLV_GROUP / 4; ++k)
+            q[k] = *reinterpret_cast<const float4 *>(nlv + p0 + 4 * k);
+#pragma unroll
+        for (int k = 0; k < NLV_GROUP; ++k) {
+            run += sample_weight((&q[k / 4].x)[k % 4], base);
+            at += run <= t ? 1 : 0;
+        }
+    } else {
+        for (int k = 0; k < NLV_GROUP && p0 + k < n; ++k) {
+            run += sample_weight(nlv[p0 + k], base);
+            at += run <= t ? 1 : 0;
+        }
+    }
+    const int p = (int)p0 + at, x = p % W, y = p / W;
     const double s = s_max - (s_max - s_min) * (double)nlv[p];
     float *row = params + (size_t)i * 8;
     row[0] = (float)x;
@@ -404,21 +567,47 @@ k_reinit(float *__restrict__ params, float *__restrict__ m, float *__restrict__ 
 size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct SaLayout {
-    size_t minmax, bmm, lv, cdf, bsum, total;
+    size_t minmax, bmm, lv, gsum, bsum, total;
 };
+
+// Rows per wave of k_local_var: 8, or 2 (more rows of halo per output) where 8 would leave the
+// chip without two workgroups per compute unit.
+int lv_rows(int H, int W)
+{
+    const long long wgs = (long long)((W + LV_W - 1) / LV_W) * ((H + 31) / 32);
+    return wgs >= 512 ? 8 : 2;
+}
 
 SaLayout sa_layout(long long npix, int H, int W)
 {
     SaLayout L;
-    const long long nb = (npix + SCAN_BLOCK - 1) / SCAN_BLOCK;
-    const long long nblk = (long long)((W + LV_T - 1) / LV_T) * ((H + LV_T - 1) / LV_T);
+    const long long nb = (npix + NLV_BLOCK - 1) / NLV_BLOCK;
+    const int rows = 4 * lv_rows(H, W);
+    const long long nblk = (long long)((W + LV_W - 1) / LV_W) * ((H + rows - 1) / rows);
     L.minmax = 0;
     L.bmm = up256(16);
     L.lv = L.bmm + up256(16 * (size_t)nblk);
-    L.cdf = L.lv + up256(8 * (size_t)npix);
-    L.bsum = L.cdf + up256(8 * (size_t)npix);
+    L.gsum = L.lv + up256(8 * (size_t)npix);
+    L.bsum = L.gsum + up256(8 * 64 * (size_t)nb);
     L.total = L.bsum + up256(8 * (size_t)nb);
     return L;
+}
+
+template <int R>
+void launch_local_var(hipStream_t st, const dim3 &grid, const float *img, int H, int W, int h,
+                      double *lv, unsigned long long *bmm)
+{
+    auto run = [&](auto kern) { kern<<<grid, 256, 0, st>>>(img, H, W, lv, bmm); };
+    switch (h) {
+    case 0: run(k_local_var<0, R>); break;
+    case 1: run(k_local_var<1, R>); break;
+    case 2: run(k_local_var<2, R>); break;
+    case 3: run(k_local_var<3, R>); break;
+    case 4: run(k_local_var<4, R>); break;
+    case 5: run(k_local_var<5, R>); break;
+    case 6: run(k_local_var<6, R>); break;
+    default: run(k_local_var<7, R>); break;
+    }
 }
 
 int launched() { return hipGetLastError() == hipSuccess ? DBMP_OK : DBMP_EHIP; }
@@ -448,20 +637,27 @@ int dbmp_blur_atlas(dbmp_aids_stream stream, const void *atlas, int B, int Hb, i
     double w[2 * BLUR_RMAX + 1], sum = 0.0;
     for (int d = -r; d <= r; ++d) sum += (w[d + r] = exp(-(double)d * d / (2.0 * sigma * sigma)));
     for (int d = -r; d <= r; ++d) t.w[d + r] = (float)(w[d + r] / sum);
+    // the sizes accepted are those whose band fits in 48 KB without the columns of zeros; with
+    // them a band needs at most 53 KB
     int band = BLUR_LDS_BYTES / (8 * Wb) - 2 * r;
-    if (band > 64) band = 64;
     if (band < 1) return DBMP_EINVAL;  // the band does not fit in LDS
-    const size_t lds = 8 * (size_t)(band + 2 * r) * Wb;
+    const long long fill = ((long long)B * Hb + 511) / 512;  // rows per workgroup of 512
+    band = (int)std::min<long long>(std::min(band, 64), std::max<long long>(fill, 8));
+    const size_t lds = 4 * (size_t)(band + 2 * r) * (2 * Wb + 2 * r);
     const dim3 grid((Hb + band - 1) / band, B);
     hipStream_t st = (hipStream_t)stream;
-    if (atlas_dtype == DBMP_F32)
-        k_blur<float><<<grid, 256, lds, st>>>((const float *)atlas, (float *)out, Hb, Wb, band, t);
-    else if (atlas_dtype == DBMP_F16)
-        k_blur<_Float16><<<grid, 256, lds, st>>>((const _Float16 *)atlas, (_Float16 *)out, Hb, Wb,
-                                                  band, t);
-    else
-        k_blur<uint16_t><<<grid, 256, lds, st>>>((const uint16_t *)atlas, (uint16_t *)out, Hb, Wb,
-                                                  band, t);
+    auto run = [&](auto texel_of, auto kern) {
+        using TexT = decltype(texel_of);
+        kern<<<grid, 256, lds, st>>>((const TexT *)atlas, (TexT *)out, Hb, Wb, band, t);
+    };
+    auto run_r = [&](auto texel_of) {
+        using TexT = decltype(texel_of);
+        if (r == 3) run(texel_of, k_blur<TexT, 3>);
+        else run(texel_of, k_blur<TexT, 0>);
+    };
+    if (atlas_dtype == DBMP_F32) run_r(float{});
+    else if (atlas_dtype == DBMP_F16) run_r(_Float16{});
+    else run_r(uint16_t{});
     return launched();
 }
 
@@ -489,24 +685,34 @@ int dbmp_sa_init(dbmp_aids_stream stream, const float *target, int H, int W, int
     auto *minmax = (unsigned long long *)(ws + L.minmax);
     auto *bmm = (unsigned long long *)(ws + L.bmm);
     auto *lv = (double *)(ws + L.lv);
-    auto *cdf = (long long *)(ws + L.cdf);
+    auto *gsum = (long long *)(ws + L.gsum);
     auto *bsum = (long long *)(ws + L.bsum);
     hipStream_t st = (hipStream_t)stream;
-    const dim3 lvg((W + LV_T - 1) / LV_T, (H + LV_T - 1) / LV_T);
-    k_local_var<<<lvg, 256, 0, st>>>(target, H, W, win / 2, lv, bmm);
-    k_lv_minmax<<<1, 1024, 0, st>>>(bmm, (int)(lvg.x * lvg.y), minmax);
-    const unsigned g = (unsigned)((npix + 255) / 256);
-    k_nlv<<<g, 256, 0, st>>>(lv, npix, minmax, base, nlv_out, cdf);
-    const int nb = (int)((npix + SCAN_BLOCK - 1) / SCAN_BLOCK);
-    k_scan_blocks<<<nb, 256, 0, st>>>(cdf, npix, bsum);
-    if (nb > 1) {
-        k_scan_sums<<<1, 1024, 0, st>>>(bsum, nb);
-        k_scan_add<<<g, 256, 0, st>>>(cdf, npix, bsum);
+    const int rows = lv_rows(H, W);
+    const dim3 lvg((W + LV_W - 1) / LV_W, (H + 4 * rows - 1) / (4 * rows));
+    if (rows == 8) launch_local_var<8>(st, lvg, target, H, W, win / 2, lv, bmm);
+    else launch_local_var<2>(st, lvg, target, H, W, win / 2, lv, bmm);
+    int nslots = (int)(lvg.x * lvg.y);
+    if (nslots > 2048) {  // too many for every workgroup of k_nlv to read
+        k_lv_minmax<<<1, 1024, 0, st>>>(bmm, nslots, minmax);
+        bmm = minmax;
+        nslots = 1;
     }
-    if (N > 0)
-        k_sa_sample<<<(N + 255) / 256, 256, 0, st>>>(cdf, npix, nlv_out, target, H, W, u_pos,
-                                                     u_theta, z_col, N, s_min, s_max, nu_init,
-                                                     sigma_c, params_out);
+    const int nb = (int)((npix + NLV_BLOCK - 1) / NLV_BLOCK);
+    k_nlv<<<nb, 256, 0, st>>>(lv, npix, bmm, nslots, base, nlv_out, gsum, bsum);
+    if (N > 0) {
+        auto run = [&](auto kern) {
+            kern<<<(N + 255) / 256, 256, 0, st>>>(gsum, bsum, nb, npix, base, nlv_out, target, H, W,
+                                                  u_pos, u_theta, z_col, N, s_min, s_max, nu_init,
+                                                  sigma_c, params_out);
+        };
+        if (nb > BSUM_LDS) {
+            k_scan_sums<<<1, 1024, 0, st>>>(bsum, nb);
+            run(k_sa_sample<true>);
+        } else {
+            run(k_sa_sample<false>);
+        }
+    }
     return launched();
 }
 
