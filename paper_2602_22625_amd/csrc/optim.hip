@@ -87,15 +87,8 @@ k_adam(float *__restrict__ p, float *__restrict__ g, float *__restrict__ m,
        int *__restrict__ step, unsigned int *__restrict__ done, int zero_grad)
 {
     const int t = *step + 1;
-    // bias corrections 1 - beta^t, evaluated in float64 once per workgroup (a float64 pow costs
-    // a wave hundreds of instructions; per element it dominated the kernel)
-    __shared__ float s_c[2];
-    if (threadIdx.x == 0) {
-        s_c[0] = (float)(1.0 - pow((double)b1, (double)t));
-        s_c[1] = (float)(1.0 - pow((double)b2, (double)t));
-    }
-    __syncthreads();
-    const AdamCoef a{lr, b1, b2, eps, s_c[0], s_c[1]};
+    const AdamCoef a{lr, b1, b2, eps, (float)(1.0 - beta_pow((double)b1, t)),
+                     (float)(1.0 - beta_pow((double)b2, t))};
     const long long first = (long long)blockIdx.x * ADAM_THREADS + threadIdx.x;
     const long long stride = (long long)gridDim.x * ADAM_THREADS;
     for (long long i = first; i < n4 / 4; i += stride) {

@@ -70,7 +70,7 @@ __device__ __forceinline__ TileGeom<TS> tile_geom(int tile, const ImgDev *__rest
                                                   int n_images)
 {
     TileGeom<TS> tg;
-    tg.b = find_by_tile(imgs, n_images, tile);
+    tg.b = find_image(n_images, tile, [&](int i) { return imgs[i].tile_off; });
     tg.D = imgs[tg.b];
     const int lt = tile - tg.D.tile_off;
     const int tx = lt % tg.D.ntx, ty = lt / tg.D.ntx;
