@@ -521,20 +521,21 @@ k_raster_fwd(const PrimRec *__restrict__ recs, int *__restrict__ lists, int list
     __shared__ float s_loss[TS * TS / 64];
     __shared__ float s_grad[FUSED ? BATCH * 8 : 1];  // the backward's per-entry partial sums
     if constexpr (FUSED) {
+        // (the walk's barriers lie between this and the sums' first use)
         for (int i = threadIdx.x; i < BATCH * 8; i += NT) s_grad[i] = 0.f;
-        __syncthreads();
     }
     const TexT *atlas = atlas_g;
     if constexpr (LDSA) atlas = stage_atlas<TexT>(atlas_g, atl_bytes);
     auto tile_body = [&](const int tile) {
+        // What needs the tile's number alone is requested before the count is known: the image,
+        // the target pixel and, in the pipelined build, whose few waves cannot hide a latency, the
+        // list's first 64 entries (its capacity is a multiple of 32; those past the count are not
+        // used): with the one-wave sort, 22.3 -> 21.4 us at 512 x 512. Where waves hide it, the
+        // entries read in vain cost more (1,234 against 1,218 us per step of 64 uneven fits).
+        int *seg = lists + (size_t)tile * list_cap;
+        const bool spec = PIPE && threadIdx.x < 64 && (int)threadIdx.x < list_cap;
+        const int entry = spec ? seg[threadIdx.x] : 0;
         const int n = tile_count[tile];
-        __syncthreads();  // every lane has read the count before it is re-armed
-        if (threadIdx.x == 0) {
-            tile_count[tile] = 0;  // ready for the next forward's appends
-            tile_len[tile] = n;    // for the backward
-            atomicMax(list_max + (blockIdx.x & (DBMP_COUNTER_SLOTS - 1)), n);  // statistic
-        }
-        if (n > list_cap) return;  // this tile's list did not fit (reported by dbmp_check)
         const TileGeom<TS> tg = tile_geom<TS>(tile, imgs, n_images);
         // the fused step's target pixel, requested now so that its latency passes during the
         // walks (it is used after the forward, to form dL/dI)
@@ -550,11 +551,35 @@ k_raster_fwd(const PrimRec *__restrict__ recs, int *__restrict__ lists, int list
             tq2 = tp[2 * tplane];
             asm volatile("" ::: "memory");
         }
-        int *seg = lists + (size_t)tile * list_cap;
+        __syncthreads();  // every lane has read the count before it is re-armed
+        if (threadIdx.x == 0) {
+            tile_count[tile] = 0;  // ready for the next forward's appends
+            tile_len[tile] = n;    // for the backward
+            atomicMax(list_max + (blockIdx.x & (DBMP_COUNTER_SLOTS - 1)), n);  // statistic
+        }
+        if (n > list_cap) return;  // this tile's list did not fit (reported by dbmp_check)
         const bool in_lds = n <= CAP;
 
         // ---- sort the tile's list front to back (index order) and write it back -----------------
-        if (in_lds) {
+        if (n <= 64) {
+            // one wave, no barrier between its steps (its LDS operations are in order): each lane
+            // counts the entries below its own (distinct primitive ids)
+            if (threadIdx.x < 64) {
+                const int v = (int)threadIdx.x < n ? (PIPE ? entry : seg[threadIdx.x]) : INT_MAX;
+                s_ids[threadIdx.x] = v;
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                int rank = 0;
+                for (int k = 0; k < n; k += 4) {
+                    const int4 q = *reinterpret_cast<const int4 *>(&s_ids[k]);
+                    rank += (q.x < v) + (q.y < v) + (q.z < v) + (q.w < v);
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                if ((int)threadIdx.x < n) {
+                    s_ids[rank] = v;
+                    seg[rank] = v;
+                }
+            }
+        } else if (in_lds) {
             for (int i = threadIdx.x; i < n + 4; i += NT) s_ids[i] = i < n ? seg[i] : INT_MAX;
             __syncthreads();
             if (n <= NT) {  // rank sort: entries are distinct primitive ids

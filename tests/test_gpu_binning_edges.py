@@ -1,8 +1,10 @@
-"""Edges of the binning: images searched 64 at a time, Adam's bias corrections at any step count."""
+"""Edges of the binning and of the rasteriser's list sort: images searched 64 at a time, lists
+around the one-wave sort's 64 entries, Adam's bias corrections at any step count."""
 import numpy as np
 import pytest
 import torch
 
+import oracle
 from paper_2602_22625_amd import capi, synth
 from paper_2602_22625_amd.render import Renderer
 
@@ -49,6 +51,30 @@ def test_image_search(n_images):
         Rs.check()
         assert torch.equal(img[3 * x0:3 * (x0 + H * W)], i1.reshape(-1)), k
         assert torch.equal(alp[x0:x0 + H * W], a1.reshape(-1)), k
+
+
+# around a list's smallest capacity (32), a wave, and the capacities that follow
+@pytest.mark.parametrize("tile", [8, 16, 32])
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 63, 64, 65, 96])
+def test_short_lists(n, tile):
+    """One tile whose list has n entries, at the smallest capacity that holds them: the pipelined
+    build alone, the one-cell build beside a 1024 x 1024 canvas, both against float64."""
+    p = _scene(n, tile, tile, 7 * n + tile, 2.0 * tile, 3.0 * tile)  # boxes over the whole tile
+    atlas = synth.soft_disk(16)[None].astype(np.float32)
+    ref, _ = oracle.render(p, np.zeros(n, np.int32), atlas, tile, tile)
+    P, A = torch.tensor(p, device="cuda"), torch.tensor(atlas, device="cuda")
+    idx = torch.zeros(n, dtype=torch.int32, device="cuda")
+    bg = torch.ones(2, 3, device="cuda")
+    R1, R2 = Renderer(list_capacity=n), Renderer(list_capacity=n)
+    i1, _ = R1.render(P, idx, A, tile, tile, bg[0].contiguous(), 1.0, tile)
+    R1.check()
+    assert R1.longest_list() == n
+    descs = [(tile, tile, n, 0, 0), (1024, 1024, 0, n, tile * tile)]
+    i2, _ = R2.render_batched(descs, P, idx, A, bg, 1.0, tile)
+    R2.check()
+    assert torch.equal(i1.reshape(-1), i2[:3 * tile * tile])
+    err = np.abs(i1.double().cpu().numpy() - ref).max() / max(np.abs(ref).max(), 1e-12)
+    assert err <= 1e-5
 
 
 @pytest.mark.parametrize("t", [1, 2, 1000, 123456, 2 ** 30])
