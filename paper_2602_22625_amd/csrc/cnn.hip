@@ -680,6 +680,9 @@ int dbmp_cnn_linear_forward(void *stream, const uint16_t *x, int B, int K, const
                             const float *bias, int N, int relu, uint16_t *y, float *y32)
 {
     if (!x || !w || (!y && !y32) || B < 1 || K < 8 || (K & 7) || N < 1) return DBMP_CNN_EINVAL;
+    hipError_t e;
+    if (linear_forward_direct((hipStream_t)stream, x, B, K, w, bias, N, relu, y, y32, &e))
+        return status(e);
     LPlain la{x, K, B, K};
     LPlain lb{w, K, N, K};
     EAct ep{bias, relu, y, y32, N};
@@ -690,6 +693,9 @@ int dbmp_cnn_linear_backward_data(void *stream, const uint16_t *dz, int B, int N
                                   const uint16_t *wt, int K, const uint16_t *mask, uint16_t *dx)
 {
     if (!dz || !wt || !dx || B < 1 || N < 8 || (N & 7) || K < 1) return DBMP_CNN_EINVAL;
+    hipError_t e;
+    if (linear_backward_data_direct((hipStream_t)stream, dz, B, N, wt, K, mask, dx, &e))
+        return status(e);
     LPlain la{dz, N, B, N};
     LPlain lb{wt, N, K, N};  // wt [K][N]
     EMask ep{mask, dx, K};
@@ -702,8 +708,9 @@ int dbmp_cnn_linear_backward_weight(void *stream, const uint16_t *x, const uint1
     if (!x || !dz || !dw || B < 1 || K < 1 || N < 1) return DBMP_CNN_EINVAL;
     EAdd ep{dw, K};
     hipStream_t st = (hipStream_t)stream;
-    const int sp = splits_for(N, K, B);
     hipError_t e;
+    if (linear_backward_weight_direct(st, x, dz, B, K, N, dw, db, &e)) return status(e);
+    const int sp = splits_for(N, K, B);
     // A(n, b) = dz[b][n], B(k, b) = x[b][k]
     if (N % 8 == 0 && K % 8 == 0 && ((uintptr_t)dz & 15) == 0 && ((uintptr_t)x & 15) == 0)
         e = gemm(st, LTrans<TVEC>{dz, N, N, B}, LTrans<TVEC>{x, K, K, B}, ep, N, K, B, sp);

@@ -1,5 +1,6 @@
 // Direct convolution kernels of the learned initialiser (3x3, stride 2, padding 1; NHWC bfloat16,
-// float32 accumulation): forward and input gradient.
+// float32 accumulation): forward and input gradient. Its dense layers run on the same kernel, a row
+// in the place of a pixel and a run of C inputs in that of a tap.
 //
 // One wave computes MT x 16 pixels by NT x 16 channels with v_mfma_f32_16x16x32_bf16, the weights
 // as the A operand (rows = channels) and the pixels as B (columns = pixels), a workgroup four
@@ -30,6 +31,8 @@
 //   16^2 x 256 -> 256  11 (39), 16 (38)    8^2 x 256 -> 256    6 (39),  7 (25)
 // The first two move 134 and 100 MB (167 MB for the gradient): 26, 20 and 33 us at the rate of a
 // large copy, which bounds them; the others are bound by the latency of their stages.
+// Dense layers at 1,024 rows (64 images; 256 -> 512 and 512 -> 512, latency): forward 4.7 (8.5) and
+// 5.0 (11.6), input gradient 3.9 (9.6) and 4.7 (9.8).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -47,7 +50,10 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
 typedef uint16_t u16;
 
-enum { FWD = 0, DGRAD = 1 };
+// Convolutions, and the dense layers' y = act(x w^T + bias) and dx = [mask > 0] dz wt^T.
+enum { FWD = 0, DGRAD = 1, LFWD = 2, LDGRAD = 3 };
+constexpr bool is_lin(int mode) { return mode >= LFWD; }
+constexpr bool is_fwd(int mode) { return mode == FWD || mode == LFWD; }
 
 struct ConvArgs {
     const u16 *src;    // FWD: x [B][H][W][C]; DGRAD: dz [B][OH][OW][C]
@@ -60,6 +66,7 @@ struct ConvArgs {
     int H, W, OH, OW;  // H = 2 OH, W = 2 OW
     int P, N;          // P = B OH OW pixels (FWD) or 2 x 2 quads (DGRAD)
     unsigned src_bytes;
+    int taps;          // dense layers: runs of C inputs (H = W = OH = OW = 1)
 };
 
 // An offset past every buffer (sizes stay below 2^31 bytes); the instruction's immediate is added
@@ -118,7 +125,7 @@ __device__ __forceinline__ void store_tile(const ConvArgs &a, const floatx4 (&ac
 {
     constexpr int NP = (NT + 1) / 2, NV = NT == 1 ? 4 : 8;
     uintx4 msk[MT][NP];
-    if (MODE == DGRAD && a.mask) {
+    if (!is_fwd(MODE) && a.mask) {
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
@@ -137,7 +144,7 @@ __device__ __forceinline__ void store_tile(const ConvArgs &a, const floatx4 (&ac
     for (int q = 0; q < NP; ++q) {
         const int n = n0 + 32 * q + (NT == 1 ? 4 : 8) * g;
         float b[NV];
-        if (MODE == FWD) {
+        if (is_fwd(MODE)) {
 #pragma unroll
             for (int j = 0; j < NV; ++j) b[j] = a.bias ? a.bias[n + j] : 0.f;
         }
@@ -148,7 +155,7 @@ __device__ __forceinline__ void store_tile(const ConvArgs &a, const floatx4 (&ac
 #pragma unroll
             for (int j = 0; j < NV; ++j) {
                 v[j] = acc[mt][NT == 1 ? 0 : 2 * q + (j >> 2)][j & 3];
-                if (MODE == FWD) {
+                if (is_fwd(MODE)) {
                     if (a.bias) v[j] += b[j];
                     if (a.relu) v[j] = fmaxf(v[j], 0.f);
                 } else if (a.mask) {
@@ -158,7 +165,7 @@ __device__ __forceinline__ void store_tile(const ConvArgs &a, const floatx4 (&ac
                 }
             }
             const size_t i = (size_t)(pix[mt] + shift) * a.N + n;
-            if (MODE == DGRAD || a.out) {
+            if (!is_fwd(MODE) || a.out) {
                 if constexpr (NT == 1)
                     *reinterpret_cast<uint2 *>(a.out + i) =
                         make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
@@ -167,7 +174,7 @@ __device__ __forceinline__ void store_tile(const ConvArgs &a, const floatx4 (&ac
                         make_uint4(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]),
                                    pack_bf16(v[4 % NV], v[5 % NV]), pack_bf16(v[6 % NV], v[7 % NV]));
             }
-            if (MODE == FWD && a.out32) {
+            if (is_fwd(MODE) && a.out32) {
 #pragma unroll
                 for (int j = 0; j < NV; j += 4)
                     *reinterpret_cast<float4 *>(a.out32 + i + j) =
@@ -213,14 +220,15 @@ __device__ __forceinline__ void copy_to_lds(GChar *p, u16 *dst)
                                      (__attribute__((address_space(3))) void *)dst, 16, 0, 0);
 }
 
-// C = 32 NCH channels of K per tap.
+// C = 32 NCH channels of K per tap; dense layers: a.taps runs of C inputs per row.
 template <int MODE, int NCH, int MT, int NT>
 __global__ void __launch_bounds__(256, 4) k_conv(ConvArgs a)
 {
-    constexpr int C = 32 * NCH, GC = stage_chunks(NCH, MT, NT), SPT = NCH / GC, NS = 9 * SPT;
+    constexpr int C = 32 * NCH, GC = stage_chunks(NCH, MT, NT), SPT = NCH / GC;
     constexpr int FR = GC * NT, FP = GC * MT;  // weight and (per wave) pixel fragments of a stage
     constexpr int RING = ring(NCH, MT, NT), D = RING - 1;  // stages in flight
     constexpr int SLOT = (FR + 4 * FP) * 512;
+    const int taps = is_lin(MODE) ? a.taps : 9, stages = taps * SPT;
     __shared__ __attribute__((aligned(1024))) u16 s_st[RING * SLOT];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 15, g = lane >> 4;
@@ -229,13 +237,19 @@ __global__ void __launch_bounds__(256, 4) k_conv(ConvArgs a)
     // as a copier the lane takes row cr and its 16-byte group cg
     const int cr = lane >> 2, cg = (lane & 3) ^ (cr >> 2);
     // (a wave's weight fragments all have nt = wave % NT: NT divides 4)
-    GChar *wp = (GChar *)(a.w + (size_t)(n0 + frag_chan<NT>(wave % NT, cr)) * 9 * C + cg * 8);
+    GChar *wp = (GChar *)(a.w + (size_t)(n0 + frag_chan<NT>(wave % NT, cr)) * (taps * C) + cg * 8);
     GChar *zp = (GChar *)g_zeros;
     GChar *pp[MT];     // the copied pixel's channels at the centre tap
     bool ey[MT], ex[MT];  // the taps with ky = 0 / kx = 0 lie outside the image
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
-        const unsigned i = (unsigned)min(p0 + mt * 16 + cr, a.P - 1), row = i / (unsigned)a.OW;
+        const unsigned i = (unsigned)min(p0 + mt * 16 + cr, a.P - 1);
+        if constexpr (is_lin(MODE)) {
+            pp[mt] = (GChar *)(a.src + (size_t)i * (unsigned)(taps * C) + cg * 8);
+            ey[mt] = ex[mt] = false;
+            continue;
+        }
+        const unsigned row = i / (unsigned)a.OW;
         const int x = (int)(i - row * (unsigned)a.OW), b = (int)(row / (unsigned)a.OH);
         const int y = (int)(row - (unsigned)b * (unsigned)a.OH);
         const size_t at = MODE == FWD ? ((size_t)b * a.H + 2 * y) * a.W + 2 * x : i;
@@ -245,7 +259,7 @@ __global__ void __launch_bounds__(256, 4) k_conv(ConvArgs a)
     }
     // stage s's copies into its slot: the weights dealt over the waves, each wave's own pixels
     auto copy_stage = [&](int t, int c0, int slot) {
-        const int ky = tap_ky<MODE>(t), kx = tap_kx<MODE>(t);
+        const int ky = is_lin(MODE) ? 0 : tap_ky<MODE>(t), kx = is_lin(MODE) ? t : tap_kx<MODE>(t);
         u16 *dst = s_st + slot * SLOT;
 #pragma unroll
         for (int i = 0; i < (FR + 3) / 4; ++i) {
@@ -253,11 +267,12 @@ __global__ void __launch_bounds__(256, 4) k_conv(ConvArgs a)
             if (FR % 4 != 0 && f >= FR) break;
             copy_to_lds(wp + ((ky * 3 + kx) * C + (c0 + f / NT) * 32) * 2, dst + f * 512);
         }
-        const int delta = MODE == FWD ? ((ky - 1) * a.W + kx - 1) * (2 * C)
-                                      : ((ky == 0) * a.OW + (kx == 0)) * (2 * C);
+        const int delta = is_lin(MODE) ? t * (2 * C)
+                          : MODE == FWD ? ((ky - 1) * a.W + kx - 1) * (2 * C)
+                                        : ((ky == 0) * a.OW + (kx == 0)) * (2 * C);
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
-            const bool out = (ky == 0 && ey[mt]) || (kx == 0 && ex[mt]);
+            const bool out = !is_lin(MODE) && ((ky == 0 && ey[mt]) || (kx == 0 && ex[mt]));
 #pragma unroll
             for (int c = 0; c < GC; ++c)
                 copy_to_lds(out ? zp : pp[mt] + delta + (c0 + c) * 64,
@@ -265,7 +280,8 @@ __global__ void __launch_bounds__(256, 4) k_conv(ConvArgs a)
         }
     };
 #pragma unroll
-    for (int s = 0; s < D; ++s) copy_stage(s / SPT, s % SPT * GC, s);
+    for (int s = 0; s < D; ++s)
+        if (!is_lin(MODE) || s < stages) copy_stage(s / SPT, s % SPT * GC, s);
     // this lane's output pixels (DGRAD: pixel (2 hy, 2 hx) of the quad), or -1
     int opix[MT];
 #pragma unroll
@@ -280,8 +296,8 @@ __global__ void __launch_bounds__(256, 4) k_conv(ConvArgs a)
     floatx4 acc[MT][NT];
     const int roff = r * 32 + ((g ^ (r >> 2)) & 3) * 8;  // the operand's place in a fragment
     int slot = 0, slot_in = D;
-    for (int t = 0; t < 9; ++t) {
-        if (t == 0 || ends_class<MODE>(t - 1)) {
+    for (int t = 0; t < taps; ++t) {
+        if (t == 0 || (!is_lin(MODE) && ends_class<MODE>(t - 1))) {
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
@@ -292,7 +308,7 @@ __global__ void __launch_bounds__(256, 4) k_conv(ConvArgs a)
             // the wave's copies of this stage have arrived (OPS: the least a later stage issues),
             // then everyone's; and everyone has read the slot that the next copies overwrite
             constexpr int OPS = FR / 4 + FP;
-            if (t * SPT + c + D - 1 < NS) stage_barrier<(D - 1) * OPS>();
+            if (t * SPT + c + D - 1 < stages) stage_barrier<(D - 1) * OPS>();
             else stage_barrier<0>();
             const u16 *sw = s_st + slot * SLOT + roff, *sp = sw + (FR + wave * FP) * 512;
             bf16x8 wf[NT], pf[MT];
@@ -305,7 +321,7 @@ __global__ void __launch_bounds__(256, 4) k_conv(ConvArgs a)
                     pf[mt] = *reinterpret_cast<const bf16x8 *>(sp + (k * MT + mt) * 512);
             };
             read_chunk(0);  // in flight while the copies are issued
-            if (t * SPT + c + D < NS)
+            if (t * SPT + c + D < stages)
                 copy_stage(t + (c + D) / SPT, (c + D) % SPT * GC, slot_in);
 #pragma unroll
             for (int k = 0; k < GC; ++k) {
@@ -320,7 +336,7 @@ __global__ void __launch_bounds__(256, 4) k_conv(ConvArgs a)
             if (++slot == RING) slot = 0;
             if (++slot_in == RING) slot_in = 0;
         }
-        if (ends_class<MODE>(t))
+        if (is_lin(MODE) ? t == taps - 1 : ends_class<MODE>(t))
             store_tile<MODE, MT, NT>(
                 a, acc, opix, MODE == DGRAD ? (class_of(t) >> 1) * a.W + (class_of(t) & 1) : 0,
                 n0, g);
@@ -450,6 +466,20 @@ bool launch_c(const ConvArgs &a, int C, hipStream_t st)
     return false;
 }
 
+// A dense layer of K inputs, as runs of the widest C that divides K: a run's stages are unrolled, its
+// end costs a branch.
+template <int MODE>
+bool launch_lin(const uint16_t *x, long long B, int K, const uint16_t *w, const float *bias,
+                const uint16_t *mask, int N, int relu, uint16_t *y, float *y32, hipStream_t st)
+{
+    if (B > (1 << 30) || K % 32 != 0 || N % 16 != 0) return false;
+    if (!aligned16(x) || !aligned16(w) || !aligned16(mask) || !aligned16(y) || !aligned16(y32))
+        return false;
+    const int C = std::min(K & -K, 256);
+    const ConvArgs a{x, w, bias, mask, y, y32, relu, 1, 1, 1, 1, (int)B, N, 0, K / C};
+    return launch_c<MODE>(a, C, st);
+}
+
 // Buffers a 31-bit byte offset addresses (with room for a tap and an immediate past the end).
 constexpr long long MAX_BYTES = (1LL << 31) - (1LL << 24);
 
@@ -463,7 +493,7 @@ bool conv_forward_direct(hipStream_t st, const uint16_t *x, int B, int H, int W,
     if (bytes > MAX_BYTES || P > (1 << 30) || Cout % 16 != 0) return false;
     if (!aligned16(x) || !aligned16(w) || !aligned16(y) || !aligned16(y32)) return false;
     ConvArgs a{x, w, bias, nullptr, y, y32, relu, H, W, H / 2, W / 2, (int)P, Cout,
-               (unsigned)bytes};
+               (unsigned)bytes, 0};
     if (Cin == 8) {
         int tiles, grid, per;
         run_of(a.P, 4, 8 * N_CU, &tiles, &grid, &per);
@@ -486,8 +516,26 @@ bool conv_backward_data_direct(hipStream_t st, const uint16_t *dz, int B, int H,
     if (bytes > MAX_BYTES || 4 * P > (1LL << 30) || Cin % 16 != 0) return false;
     if (!aligned16(dz) || !aligned16(wt) || !aligned16(mask) || !aligned16(dx)) return false;
     ConvArgs a{dz, wt, nullptr, mask, dx, nullptr, 0, H, W, H / 2, W / 2, (int)P, Cin,
-               (unsigned)bytes};
+               (unsigned)bytes, 0};
     if (!launch_c<DGRAD>(a, Cout, st)) return false;
+    *err = hipGetLastError();
+    return true;
+}
+
+bool linear_forward_direct(hipStream_t st, const uint16_t *x, int B, int K, const uint16_t *w,
+                           const float *bias, int N, int relu, uint16_t *y, float *y32,
+                           hipError_t *err)
+{
+    if (!launch_lin<LFWD>(x, B, K, w, bias, nullptr, N, relu, y, y32, st)) return false;
+    *err = hipGetLastError();
+    return true;
+}
+
+bool linear_backward_data_direct(hipStream_t st, const uint16_t *dz, int B, int N,
+                                 const uint16_t *wt, int K, const uint16_t *mask, uint16_t *dx,
+                                 hipError_t *err)
+{
+    if (!launch_lin<LDGRAD>(dz, B, N, wt, nullptr, mask, K, 0, dx, nullptr, st)) return false;
     *err = hipGetLastError();
     return true;
 }

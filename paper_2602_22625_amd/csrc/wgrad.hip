@@ -24,6 +24,8 @@
 // 39, 30, 24, 25, 17 and 11 us, biases included. The first two read 134 and 101 MB, 26 and 20 us at
 // the rate of a large copy; the deeper ones have few steps per wave (4 to 16), so a large part of
 // theirs is the first loads' latency and the sums' way out.
+// The dense layers' gradients (dw[n][k] += sum over rows of dz[row][n] x[row][k]) are the same with
+// rows for pixels and one tap: at 1,024 rows, 256 -> 512 and 512 -> 512, 5.4 (15.2) and 6.5 us (17.6).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -141,19 +143,21 @@ __device__ __forceinline__ void add_bias(const floatx4 (&accb)[WM], float *s, fl
 constexpr uint32_t ONES = 0x3f803f80u;  // a pair of bf16 ones
 
 // WM channels of dz per lane (16 WM per workgroup), 32 channels of x. ROWS: the 8 output pixels of
-// a group lie in ROWS image rows (OW % (8 / ROWS) == 0).
+// a group lie in ROWS image rows (OW % (8 / ROWS) == 0); ROWS = 0: a dense layer, whose 8 rows are
+// the pixels of a 1 x 1 filter.
 template <int WM, int ROWS>
 __global__ void __launch_bounds__(256, 2) k_wgrad(WgradArgs a)
 {
-    constexpr int SUB = 8 / ROWS, COLS = 2 * SUB + 1, NF = WM * 6;
+    constexpr int NR = ROWS ? ROWS : 1, SUB = 8 / NR, COLS = ROWS ? 2 * SUB + 1 : 8;
+    constexpr int KX = ROWS ? 3 : 1, NF = WM * 2 * KX, TAPS = KX * KX;
     __shared__ __attribute__((aligned(16))) float s_red[2][NF * 256];
     __shared__ float s_b[256];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 15, g = lane >> 4;
     int split, tile;
-    place(blockIdx.x, a.tiles_m * a.tiles_n * 3, a.splits, split, tile);
-    if (split >= a.splits || tile >= a.tiles_m * a.tiles_n * 3) return;
-    const int tm = tile % a.tiles_m, ky = tile / a.tiles_m % 3, tn = tile / a.tiles_m / 3;
+    place(blockIdx.x, a.tiles_m * a.tiles_n * KX, a.splits, split, tile);
+    if (split >= a.splits || tile >= a.tiles_m * a.tiles_n * KX) return;
+    const int tm = tile % a.tiles_m, ky = tile / a.tiles_m % KX, tn = tile / a.tiles_m / KX;
     const int m0 = tm * 16 * WM, n0 = tn * 32;
     const bool bias = a.db && ky == 0 && tn == 0;
     const auto bz = __builtin_amdgcn_make_buffer_rsrc(const_cast<u16 *>(a.dz), (short)0,
@@ -162,7 +166,7 @@ __global__ void __launch_bounds__(256, 2) k_wgrad(WgradArgs a)
                                                       (int)a.x_bytes, 0x00020000);
     struct Step {
         Words<WM / 2> z[8];
-        uint32_t x[ROWS][COLS];
+        uint32_t x[NR][COLS];
     };
     auto load = [&](int step, Step &s) {
         const int gr = step * 4 + g;
@@ -171,6 +175,12 @@ __global__ void __launch_bounds__(256, 2) k_wgrad(WgradArgs a)
         const unsigned zo = in ? (p * (unsigned)a.Cout + m0 + WM * r) * 2 : OOB;
 #pragma unroll
         for (int j = 0; j < 8; ++j) s.z[j] = load_words<WM / 2>(bz, zo, j * a.Cout * 2);
+        if constexpr (ROWS == 0) {
+            const unsigned xo = in ? (p * (unsigned)a.Cin + n0 + 2 * r) * 2 : OOB;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) s.x[0][j] = load_words<1>(bx, xo, j * a.Cin * 2).w[0];
+            return;
+        }
 #pragma unroll
         for (int q = 0; q < ROWS; ++q) {
             const unsigned ps = in ? p + q * SUB : 0, row = ps / (unsigned)a.OW;
@@ -213,19 +223,21 @@ __global__ void __launch_bounds__(256, 2) k_wgrad(WgradArgs a)
                     fa[c], __builtin_bit_cast(bf16x8, one), accb[c], 0, 0, 0);
         }
 #pragma unroll
-        for (int kx = 0; kx < 3; ++kx)
+        for (int kx = 0; kx < KX; ++kx)
 #pragma unroll
             for (int cn = 0; cn < 2; ++cn) {
                 uintx4 v;
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
-                    v[q] = pair(cur.x[2 * q / SUB][2 * (2 * q % SUB) + kx],
-                                cur.x[(2 * q + 1) / SUB][2 * ((2 * q + 1) % SUB) + kx], cn);
+                    v[q] = ROWS == 0
+                               ? pair(cur.x[0][2 * q % COLS], cur.x[0][(2 * q + 1) % COLS], cn)
+                               : pair(cur.x[2 * q / SUB][2 * (2 * q % SUB) + kx],
+                                      cur.x[(2 * q + 1) / SUB][2 * ((2 * q + 1) % SUB) + kx], cn);
                 const bf16x8 fb = __builtin_bit_cast(bf16x8, v);
 #pragma unroll
                 for (int c = 0; c < WM; ++c)
-                    acc[(c * 3 + kx) * 2 + cn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                        fa[c], fb, acc[(c * 3 + kx) * 2 + cn], 0, 0, 0);
+                    acc[(c * KX + kx) * 2 + cn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        fa[c], fb, acc[(c * KX + kx) * 2 + cn], 0, 0, 0);
             }
         cur = nxt;
     }
@@ -239,9 +251,9 @@ __global__ void __launch_bounds__(256, 2) k_wgrad(WgradArgs a)
 #pragma unroll
         for (int c = 0; c < WM; ++c)
 #pragma unroll
-            for (int kx = 0; kx < 3; ++kx) {
-                const int k = ((c * 3 + kx) * 2 + cn) * 256 + at;
-                unsafeAtomicAdd(a.dw + ((size_t)(m0 + WM * row + c) * 9 + ky * 3 + kx) * a.Cin +
+            for (int kx = 0; kx < KX; ++kx) {
+                const int k = ((c * KX + kx) * 2 + cn) * 256 + at;
+                unsafeAtomicAdd(a.dw + ((size_t)(m0 + WM * row + c) * TAPS + ky * KX + kx) * a.Cin +
                                     n0 + 2 * col + cn,
                                 s_red[0][k] + s_red[1][k]);
             }
@@ -342,18 +354,21 @@ __global__ void __launch_bounds__(256, 2) k_wgrad8(WgradArgs a)
     if (a.db) add_bias<WM>(accb, s_b, a.db + m0, lane, wave);
 }
 
+constexpr long long MAX_BYTES = (1LL << 31) - (1LL << 24);  // what OOB stays beyond
+
 template <int WM, int ROWS>
 void launch(WgradArgs a, hipStream_t st)
 {
+    constexpr int KX = ROWS ? 3 : 1;
     // 512 workgroups (two per compute unit) at most, at least four steps per wave; splits a
     // multiple of 8, or 1, 2 or 4 (place)
-    const int tiles = a.tiles_m * (a.Cin == 8 ? 1 : a.tiles_n * 3), steps = (a.groups + 3) / 4;
+    const int tiles = a.tiles_m * (ROWS && a.Cin == 8 ? 1 : a.tiles_n * KX), steps = (a.groups + 3) / 4;
     int s = std::min(std::max(1, 512 / tiles), std::max(1, steps / 16));
     s = s >= 8 ? s / 8 * 8 : s >= 4 ? 4 : s >= 2 ? 2 : 1;
     a.splits = s;
     a.per_wave = (steps + 4 * s - 1) / (4 * s);
     const int blocks = s >= 8 ? s * tiles : 8 * ((tiles + 8 / s - 1) / (8 / s));
-    if constexpr (WM == 2)
+    if constexpr (WM == 2 && ROWS != 0)
         if (a.Cin == 8) return k_wgrad8<WM, ROWS><<<blocks, 256, 0, st>>>(a);
     k_wgrad<WM, ROWS><<<blocks, 256, 0, st>>>(a);
 }
@@ -364,7 +379,6 @@ bool conv_backward_weight_direct(hipStream_t st, const uint16_t *x, const uint16
                                  int H, int W, int Cin, int Cout, float *dw, float *db,
                                  hipError_t *err)
 {
-    constexpr long long MAX_BYTES = (1LL << 31) - (1LL << 24);
     const long long P = (long long)B * (H / 2) * (W / 2);
     const long long xb = 8 * P * Cin, zb = 2 * P * Cout;
     if (xb > MAX_BYTES || zb > MAX_BYTES || Cout % 32 != 0 || (Cin != 8 && Cin % 32 != 0))
@@ -375,6 +389,20 @@ bool conv_backward_weight_direct(hipStream_t st, const uint16_t *x, const uint16
                       (int)(P / 8), Cout / (wide ? 64 : 32), Cin / 32, 0, 0};
     if (wide) rows2 ? launch<4, 2>(a, st) : launch<4, 1>(a, st);
     else rows2 ? launch<2, 2>(a, st) : launch<2, 1>(a, st);
+    *err = hipGetLastError();
+    return true;
+}
+
+bool linear_backward_weight_direct(hipStream_t st, const uint16_t *x, const uint16_t *dz, int B,
+                                   int K, int N, float *dw, float *db, hipError_t *err)
+{
+    const long long xb = 2LL * B * K, zb = 2LL * B * N;
+    if (xb > MAX_BYTES || zb > MAX_BYTES || N % 32 != 0 || K % 32 != 0 || B % 8 != 0) return false;
+    if ((((uintptr_t)x | (uintptr_t)dz) & 15) != 0) return false;
+    const bool wide = N % 64 == 0;
+    const WgradArgs a{x, dz, dw, db, 1, 1, 1, 1, K, N, (unsigned)xb, (unsigned)zb, B / 8,
+                      N / (wide ? 64 : 32), K / 32, 0, 0};
+    wide ? launch<4, 0>(a, st) : launch<2, 0>(a, st);
     *err = hipGetLastError();
     return true;
 }
