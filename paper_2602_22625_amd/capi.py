@@ -86,6 +86,7 @@ def load():
         "dbmp_cnn_linear_backward_data": ([P, P, I, I, P, I, P, P], I),
         "dbmp_cnn_linear_backward_weight": ([P, P, P, I, I, I, P, P], I),
         "dbmp_cnn_cast_weights": ([P, P, I, I, I, P, P], I),
+        "dbmp_cnn_cast_layers": ([P, I, P, P, P, P, P, P], I),
         "dbmp_cnn_pack_input": ([P, P, I, I, I, P], I),
         "dbmp_cnn_param_loss": ([P, P, P, P, LL, F, P, P, P, P], I),
         "dbmp_cnn_code_params": ([P, P, LL, I, I, I, F, P, P, F, I, P], I),
@@ -334,6 +335,16 @@ def dbmp_cnn_linear_backward_weight(stream, x, dz, B, K, N, dw, db):
 def dbmp_cnn_cast_weights(stream, w, R, T, C, wb, wt):
     return _cnn(load().dbmp_cnn_cast_weights(stream, ptr(w), R, T, C, ptr(wb), ptr(wt)),
                 "dbmp_cnn_cast_weights")
+
+
+def dbmp_cnn_cast_layers(stream, layers):
+    """layers: (w, R, T, C, wb, wt) of each, as dbmp_cnn_cast_weights takes them."""
+    w, R, T, C, wb, wt = zip(*layers) if layers else ((),) * 6
+    n = len(w)
+    ptrs = [(ctypes.c_void_p * n)(*[ptr(x) for x in v]) for v in (w, wb, wt)]
+    ints = [(ctypes.c_int * n)(*v) for v in (R, T, C)]
+    return _cnn(load().dbmp_cnn_cast_layers(stream, n, ptrs[0], *ints, ptrs[1], ptrs[2]),
+                "dbmp_cnn_cast_layers")
 
 
 def dbmp_cnn_pack_input(stream, img, B, H, W, x):

@@ -180,9 +180,9 @@ class InitNet:
         self.cast()
 
     def cast(self):
-        st = capi.stream_handle()
-        for (kind, R, T, C), w, wb, wt in zip(self.layers, self.w, self.wb, self.wt):
-            capi.dbmp_cnn_cast_weights(st, w, R, T, C, wb, wt)
+        capi.dbmp_cnn_cast_layers(capi.stream_handle(), [
+            (w, R, T, C, wb, wt)
+            for (kind, R, T, C), w, wb, wt in zip(self.layers, self.w, self.wb, self.wt)])
 
     def _buffers(self, B):
         if self._B == B:

@@ -483,19 +483,109 @@ static hipError_t colsum(hipStream_t st, const u16 *dz, int M, int N, float *db)
     return hipGetLastError();
 }
 
-// float32 weights [R][T][C] -> bf16 copies in [R][T][C] and transposed [C][T][R] layouts.
-__global__ void k_cast(const float *__restrict__ w, int R, int T, int C, u16 *__restrict__ wb,
-                       u16 *__restrict__ wt)
+// float32 weights [R][T][C] -> bf16 copies in [R][T][C] and transposed [C][T][R] layouts, several
+// layers in one launch. A workgroup takes a 64 x 64 tile (rows, channels) of one tap of one layer and
+// turns it in LDS, so that both copies are written along memory in 16 bytes (8 for the first): a
+// two-byte store of stride R per value left 64 cache lines per wave. The learned initialiser's eight
+// layers, 1.96 million weights: 6.4 us, 43 us as eight launches of the two-byte form.
+constexpr int CAST_LAYERS = 16, CAST_TILE = 64, CAST_PITCH = CAST_TILE + 8;
+
+struct CastLayer {
+    const float *w;
+    u16 *wb, *wt;
+    int R, T, C;
+    int first;       // its first workgroup
+    int vec;         // rows of w and wb (1) and of wt (2) start aligned for 16 and 8 bytes
+};
+struct CastArgs {
+    CastLayer l[CAST_LAYERS];
+    int n;
+};
+
+__global__ void __launch_bounds__(256) k_cast(CastArgs a)
 {
-    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    const long long n = (long long)R * T * C;
-    if (i >= n) return;
-    const int c = (int)(i % C);
-    const int t = (int)((i / C) % T);
-    const int r = (int)(i / ((long long)C * T));
-    const u16 h = f2bf(w[i]);
-    if (wb) wb[i] = h;
-    if (wt) wt[((size_t)c * T + t) * R + r] = h;
+    __shared__ __attribute__((aligned(16))) u16 s[CAST_TILE * CAST_PITCH];  // [channel][row]
+    int k = 0;
+    while (k + 1 < a.n && a.l[k + 1].first <= (int)blockIdx.x) ++k;
+    const CastLayer L = a.l[k];
+    const int tc = (L.C + CAST_TILE - 1) / CAST_TILE;
+    int q = (int)blockIdx.x - L.first;
+    const int c0 = q % tc * CAST_TILE;
+    q /= tc;
+    const int t = q % L.T, r0 = q / L.T * CAST_TILE;
+    const int cl = (threadIdx.x & 15) * 4, c = c0 + cl;
+    float4 v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int r = r0 + (threadIdx.x >> 4) + 16 * i;
+        v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (r >= L.R || c >= L.C) continue;
+        const float *w = L.w + ((size_t)r * L.T + t) * L.C + c;
+        if (L.vec & 1) {
+            v[i] = *reinterpret_cast<const float4 *>(w);
+        } else {
+            v[i].x = w[0];
+            if (c + 1 < L.C) v[i].y = w[1];
+            if (c + 2 < L.C) v[i].z = w[2];
+            if (c + 3 < L.C) v[i].w = w[3];
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int rl = (threadIdx.x >> 4) + 16 * i, r = r0 + rl;
+        const u16 h[4] = {f2bf(v[i].x), f2bf(v[i].y), f2bf(v[i].z), f2bf(v[i].w)};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) s[(cl + j) * CAST_PITCH + rl] = h[j];
+        if (!L.wb || r >= L.R || c >= L.C) continue;
+        u16 *wb = L.wb + ((size_t)r * L.T + t) * L.C + c;
+        if (L.vec & 1) {
+            *reinterpret_cast<ushort4 *>(wb) = make_ushort4(h[0], h[1], h[2], h[3]);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (c + j < L.C) wb[j] = h[j];
+        }
+    }
+    if (!L.wt) return;  // (the same for the whole workgroup)
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int ch = (threadIdx.x >> 3) + 32 * i, rl = (threadIdx.x & 7) * 8, r = r0 + rl;
+        if (c0 + ch >= L.C || r >= L.R) continue;
+        u16 *wt = L.wt + ((size_t)(c0 + ch) * L.T + t) * L.R + r;
+        const u16 *p = &s[ch * CAST_PITCH + rl];
+        if (L.vec & 2) {
+            *reinterpret_cast<uint4 *>(wt) = *reinterpret_cast<const uint4 *>(p);
+        } else {
+            for (int j = 0; j < 8; ++j)
+                if (r + j < L.R) wt[j] = p[j];
+        }
+    }
+}
+
+static hipError_t cast_layers(hipStream_t st, int n, const float *const *w, const int *R,
+                              const int *T, const int *C, uint16_t *const *wb, uint16_t *const *wt)
+{
+    for (int i0 = 0; i0 < n; i0 += CAST_LAYERS) {
+        CastArgs a{};
+        long long blocks = 0;
+        a.n = std::min(CAST_LAYERS, n - i0);
+        for (int k = 0; k < a.n; ++k) {
+            const int i = i0 + k;
+            CastLayer &L = a.l[k];
+            L = {w[i], wb[i], wt[i], R[i], T[i], C[i], (int)blocks, 0};
+            if (C[i] % 4 == 0 && ((uintptr_t)w[i] & 15) == 0 && ((uintptr_t)wb[i] & 7) == 0)
+                L.vec |= 1;
+            if (R[i] % 8 == 0 && ((uintptr_t)wt[i] & 15) == 0) L.vec |= 2;
+            blocks += (long long)((R[i] + CAST_TILE - 1) / CAST_TILE) * T[i] *
+                      ((C[i] + CAST_TILE - 1) / CAST_TILE);
+            if (blocks > INT32_MAX) return hipErrorInvalidValue;
+        }
+        k_cast<<<(unsigned)blocks, 256, 0, st>>>(a);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 // float32 images [B][3][H][W] -> bf16 NHWC [B][H][W][8] (channels 3..7 zero).
@@ -724,9 +814,16 @@ int dbmp_cnn_cast_weights(void *stream, const float *w, int R, int T, int C, uin
                           uint16_t *wt)
 {
     if (!w || (!wb && !wt) || R < 1 || T < 1 || C < 1) return DBMP_CNN_EINVAL;
-    const long long n = (long long)R * T * C;
-    k_cast<<<(unsigned)((n + 255) / 256), 256, 0, (hipStream_t)stream>>>(w, R, T, C, wb, wt);
-    return status(hipGetLastError());
+    return status(cast_layers((hipStream_t)stream, 1, &w, &R, &T, &C, &wb, &wt));
+}
+
+int dbmp_cnn_cast_layers(void *stream, int n, const float *const *w, const int *R, const int *T,
+                         const int *C, uint16_t *const *wb, uint16_t *const *wt)
+{
+    if (n < 0 || (n > 0 && (!w || !R || !T || !C || !wb || !wt))) return DBMP_CNN_EINVAL;
+    for (int i = 0; i < n; ++i)
+        if (!w[i] || (!wb[i] && !wt[i]) || R[i] < 1 || T[i] < 1 || C[i] < 1) return DBMP_CNN_EINVAL;
+    return status(cast_layers((hipStream_t)stream, n, w, R, T, C, wb, wt));
 }
 
 int dbmp_cnn_pack_input(void *stream, const float *img, int B, int H, int W, uint16_t *x)

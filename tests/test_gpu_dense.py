@@ -72,3 +72,31 @@ def test_dense_layers_exact(shape):
         assert np.array_equal(dw.cpu().numpy(), (rw + 0.5).astype(np.float32))
         if bias:
             assert np.array_equal(db.cpu().numpy(), (rb - 0.25).astype(np.float32))
+
+
+# one layer off the vector forms; all of them at once (R, T, C around the 64 x 64 tile; more layers
+# than one launch takes)
+@pytest.mark.parametrize("off", [0, 1])
+@pytest.mark.parametrize("shapes", [[(5, 1, 3)], [(64, 9, 64)],
+                                    [(32, 9, 8), (65, 1, 130), (1, 9, 64), (512, 1, 256), (24, 3, 20)],
+                                    [(8 * k, 1 + k % 3, 4 * k) for k in range(1, 20)]])
+def test_cast_layers(shapes, off):
+    g = np.random.default_rng(len(shapes))
+    layers, want = [], []
+    for R, T, C in shapes:
+        w = g.standard_normal((R, T, C)).astype(np.float32)
+        d = torch.zeros(w.size + off, device="cuda")
+        d[off:] = torch.tensor(w.reshape(-1), device="cuda")
+        wb, wt = (torch.zeros(w.size + 8, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+        layers.append((d[off:], R, T, C, wb[off:], wt[off:]))
+        want.append(bf16_round(w))
+    layers[0] = layers[0][:4] + (None,) + layers[0][5:]
+    capi.dbmp_cnn_cast_layers(capi.stream_handle(), layers)
+    torch.cuda.synchronize()
+    for k, ((_, R, T, C, wb, wt), r) in enumerate(zip(layers, want)):
+        n = R * T * C
+        assert np.array_equal(wt[:n].float().cpu().numpy(), r.transpose(2, 1, 0).reshape(-1)), k
+        assert not wt[n:].any()
+        if wb is not None:
+            assert np.array_equal(wb[:n].float().cpu().numpy(), r.reshape(-1)), k
+            assert not wb[n:].any()
