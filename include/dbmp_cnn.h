@@ -66,10 +66,6 @@ int dbmp_cnn_linear_backward_weight(void *stream, const uint16_t *x, const uint1
 int dbmp_cnn_cast_weights(void *stream, const float *w, int R, int T, int C, uint16_t *wb,
                           uint16_t *wt);
 
-/* The same for n layers (arrays of n in host memory), 16 to a launch. */
-int dbmp_cnn_cast_layers(void *stream, int n, const float *const *w, const int *R, const int *T,
-                         const int *C, uint16_t *const *wb, uint16_t *const *wt);
-
 /* float32 planar RGB images [B][3][H][W] -> bf16 NHWC [B][H][W][8], channels 3..7 zero. */
 int dbmp_cnn_pack_input(void *stream, const float *img, int B, int H, int W, uint16_t *x);
 

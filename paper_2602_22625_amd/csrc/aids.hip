@@ -589,7 +589,8 @@ SaLayout sa_layout(long long npix, int H, int W)
     L.lv = L.bmm + up256(16 * (size_t)nblk);
     L.gsum = L.lv + up256(8 * (size_t)npix);
     L.bsum = L.gsum + up256(8 * 64 * (size_t)nb);
-    L.total = L.bsum + up256(8 * (size_t)nb);
+    // never less than 16 bytes per pixel, the size that callers have always had to bring
+    L.total = std::max(L.bsum + up256(8 * (size_t)nb), L.gsum + up256(8 * (size_t)npix));
     return L;
 }
 

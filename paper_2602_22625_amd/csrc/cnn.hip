@@ -22,6 +22,7 @@
 
 #include "cnn_kernels.h"
 #include "dbmp_cnn.h"
+#include "dbmp_cnn_cast.h"
 
 namespace dbmp_cnn {
 
