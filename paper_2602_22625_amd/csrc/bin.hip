@@ -459,7 +459,7 @@ k_prep(const float *params, const int *__restrict__ idx, long long n_rows,
             if (g >= D.prim_off && g < D.prim_off + D.N) {
                 bool ok = true;
                 if (!k_ok) {
-                    atomicOr(&flags[F_S_BADIDX], 1);
+                    flags[F_S_BADIDX] = 1;
                     ok = false;
                 }
                 bool fin = true;
@@ -467,7 +467,7 @@ k_prep(const float *params, const int *__restrict__ idx, long long n_rows,
                 for (int j = 0; j < 8; ++j) fin = fin && isfinite(p[j]);
                 if (!(s > 0.0) || !isfinite(s)) fin = false;  // scale underflows or overflows
                 if (!fin) {
-                    atomicOr(&flags[F_S_NONFINITE], 1);
+                    flags[F_S_NONFINITE] = 1;
                     ok = false;
                 }
                 if (ok) {
@@ -491,7 +491,7 @@ k_prep(const float *params, const int *__restrict__ idx, long long n_rows,
                     const int Hp = Hb + 2;
                     rec.tex = k * Hp * Wp;
                     if (xlo == INT_MIN) {  // the bitmap holds a non-finite texel (read as 0)
-                        atomicOr(&flags[F_S_NONFINITE], 1);
+                        flags[F_S_NONFINITE] = 1;
                         xlo = 0;
                     }
                     if (xlo <= xhi) {

@@ -21,9 +21,11 @@ static_assert(DBMP_SCHED_GRID == SCHED_GRID && DBMP_SCHED_SORTED == SCHED_SORTED
 struct dbmp_ctx {
     int device = 0;
     std::string err;
-    Buf recs, tile_count, tile_len, lists, saveK, saveT, atlas_pad, box, imgs, flags, counter,
+    Buf recs, tile_count, tile_len, lists, saveK, saveT, atlas_pad, box, imgs, counter,
         list_max, loss_tile, order, order_hist, queue;
-    int list_cap = 0;  // entries per tile list
+    volatile int *flags = nullptr;  // F_COUNT slots in pinned host memory, written by the device
+    int *flags_dev = nullptr;       // their device address
+    int list_cap = 0;               // entries per tile list
     // launch schedule of the raster kernels (dbmp_set_schedule)
     int sched = SCHED_GRID;
     int wgs_per_cu = 4;
@@ -277,7 +279,7 @@ int render_impl(dbmp_ctx *c, hipStream_t st, const std::vector<dbmp_image_desc> 
     ba.alpha_max = alpha_max; ba.TS = tile; ba.atlas_pad = c->atlas_pad.p;
     ba.box = (int *)c->box.p; ba.recs = (PrimRec *)c->recs.p;
     ba.tile_count = (int *)c->tile_count.p; ba.lists = (int *)c->lists.p;
-    ba.list_cap = c->list_cap; ba.flags = (int *)c->flags.p; ba.pad_atlas = false;
+    ba.list_cap = c->list_cap; ba.flags = c->flags_dev; ba.pad_atlas = false;
     ba.order = c->sched != SCHED_GRID ? (int *)c->order.p : nullptr;
     ba.order_hist = (int *)c->order_hist.p;
     ba.adam = fuse.adam;
@@ -304,7 +306,7 @@ int render_impl(dbmp_ctx *c, hipStream_t st, const std::vector<dbmp_image_desc> 
     }
     ra.bg = bg; ra.bg_pp = bg_pp; ra.image = image; ra.alpha = alpha;
     ra.saveK = (int *)c->saveK.p; ra.saveT = (float *)c->saveT.p;
-    ra.flags = (const int *)c->flags.p; ra.TS = tile;
+    ra.flags = c->flags_dev; ra.TS = tile;
     ra.pair_counter = (unsigned long long *)c->counter.p;
     ra.loss_tile = (float *)c->loss_tile.p;
     ra.sched = c->sched;
@@ -356,8 +358,16 @@ int dbmp_create(dbmp_ctx **out, int device, long long list_capacity)
     c->device = device;
     c->list_cap = round_cap(list_capacity > 0 ? (int)list_capacity : 256);
     DeviceGuard g(device);
-    int rc = ensure(c, c->flags, 4 * F_COUNT, nullptr, "flags");
-    if (!rc) rc = ensure(c, c->counter, 8 * DBMP_COUNTER_SLOTS, nullptr, "counter");
+    void *fl = nullptr, *fd = nullptr;
+    if (hipHostMalloc(&fl, 4 * F_COUNT, hipHostMallocMapped) != hipSuccess) {
+        delete c;
+        return DBMP_ENOMEM;
+    }
+    c->flags = (volatile int *)fl;
+    for (int i = 0; i < F_COUNT; ++i) c->flags[i] = 0;
+    if (hipHostGetDevicePointer(&fd, fl, 0) != hipSuccess) { dbmp_destroy(c); return DBMP_EHIP; }
+    c->flags_dev = (int *)fd;
+    int rc = ensure(c, c->counter, 8 * DBMP_COUNTER_SLOTS, nullptr, "counter");
     if (!rc) rc = ensure(c, c->list_max, 4 * DBMP_COUNTER_SLOTS, nullptr, "list_max");
     if (!rc) rc = ensure(c, c->queue, 16, nullptr, "work queues");
     if (rc) { dbmp_destroy(c); return rc; }
@@ -365,8 +375,7 @@ int dbmp_create(dbmp_ctx **out, int device, long long list_capacity)
     if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, device) ==
             hipSuccess && ncu > 0)
         c->n_cu = ncu;
-    hipError_t e = hipMemset(c->flags.p, 0, 4 * F_COUNT);
-    if (e == hipSuccess) e = hipMemset(c->queue.p, 0, 16);
+    hipError_t e = hipMemset(c->queue.p, 0, 16);
     if (e == hipSuccess) e = hipMemset(c->counter.p, 0, 8 * DBMP_COUNTER_SLOTS);
     if (e == hipSuccess) e = hipMemset(c->list_max.p, 0, 4 * DBMP_COUNTER_SLOTS);
     if (e == hipSuccess) e = hipDeviceSynchronize();
@@ -382,10 +391,11 @@ int dbmp_destroy(dbmp_ctx *c)
         DeviceGuard g(c->device);
         (void)hipDeviceSynchronize();
         Buf *bs[] = {&c->recs, &c->tile_count, &c->tile_len, &c->lists, &c->saveK, &c->saveT,
-                     &c->atlas_pad, &c->box, &c->imgs, &c->flags, &c->counter, &c->list_max,
+                     &c->atlas_pad, &c->box, &c->imgs, &c->counter, &c->list_max,
                      &c->loss_tile, &c->order, &c->order_hist, &c->queue};
         for (Buf *b : bs)
             if (b->p) (void)hipFree(b->p);
+        if (c->flags) (void)hipHostFree((void *)c->flags);
     }
     delete c;
     return DBMP_OK;
@@ -642,13 +652,8 @@ int dbmp_check(dbmp_ctx *c, dbmp_stream stream)
     hipError_t e = hipStreamSynchronize((hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(c, e, "hipStreamSynchronize");
     int f[F_COUNT];
-    e = hipMemcpy(f, c->flags.p, sizeof(f), hipMemcpyDeviceToHost);
-    if (e != hipSuccess) return hip_fail(c, e, "flag readback");
-    if (f[F_S_OVERFLOW] | f[F_S_BADIDX] | f[F_S_NONFINITE]) {
-        e = hipMemset((int *)c->flags.p + F_S_OVERFLOW, 0, 3 * sizeof(int));
-        if (e == hipSuccess) e = hipDeviceSynchronize();
-        if (e != hipSuccess) return hip_fail(c, e, "flag reset");
-    }
+    for (int i = 0; i < F_COUNT; ++i)
+        if ((f[i] = c->flags[i]) != 0) c->flags[i] = 0;
     if (f[F_S_OVERFLOW])
         return fail(c, DBMP_EOVERFLOW, "a tile list exceeds the capacity of " +
                                            std::to_string(c->list_cap) +
@@ -694,7 +699,7 @@ long long dbmp_workspace_bytes(const dbmp_ctx *c)
     if (!c) return -1;
     const Buf *bufs[] = {&c->recs,      &c->tile_count, &c->tile_len,  &c->lists,
                          &c->saveK,     &c->saveT,      &c->atlas_pad, &c->box,
-                         &c->imgs,      &c->flags,      &c->counter,   &c->list_max,
+                         &c->imgs,      &c->counter,    &c->list_max,
                          &c->loss_tile, &c->order,      &c->order_hist, &c->queue};
     long long n = 0;
     for (const Buf *b : bufs) n += (long long)b->cap;
