@@ -122,35 +122,39 @@ __device__ __forceinline__ double tree_sum(At at, int i0 = 0)
     }
 }
 
-// The local variance (float64) over the (2 h + 1)^2 window clipped to the image, 64 columns by 4 R
-// rows per workgroup. Per channel: each row's window sums of values and squares along x into LDS
+// The local variance (float64) over the (2 h + 1)^2 window clipped to the image, 64 columns by NW R
+// rows per workgroup of NW waves. Per channel: each row's window sums of values and squares along x into LDS
 // (values straight from memory: a window's loads hit the same lines), then each wave adds up
 // 2 h + 1 rows of them for its R rows of outputs: about 45 float64 operations per pixel and channel
-// for a 7 x 7 window (R = 8), where summing the window afresh took 98 and as many conversions:
-// 67 us at 2048 x 2048, 176 before. Bound by latency (three waves per SIMD beside the outputs'
-// registers; the operations alone would take 27 us). Keeping the row sums in registers instead
-// took 62 us with strips of 4 rows, 79 with 8, and spilled for the larger windows.
-template <int HW, int R>
-__global__ void __launch_bounds__(256)
+// for a 7 x 7 window, where summing the window afresh took 98 and as many conversions: 58 us at
+// 2048 x 2048, 176 before. Bound by latency (the operations alone would take about 27 us), so waves
+// in flight count: 8 waves of 4 rows at 5 per SIMD, where 4 waves of 8 rows (3 per SIMD) took 67 and
+// 16 of 2 rows 87; the three channels' loop is kept rolled, which the compiler would undo for the
+// small windows at twice the registers (3 x 3: 86 us for the whole start against 54). Keeping the
+// row sums in registers instead took 62 us with strips of 4 rows, 79 with 8, and spilled for the
+// larger windows.
+template <int HW, int R, int NW>
+__global__ void __launch_bounds__(64 * NW)
 k_local_var(const float *__restrict__ img, int H, int W, double *__restrict__ lv,
             unsigned long long *__restrict__ bmm)
 {
-    constexpr int WIN = 2 * HW + 1, ROWS = 4 * R + 2 * HW;
+    constexpr int WIN = 2 * HW + 1, ROWS = NW * R + 2 * HW;
     __shared__ double s1[ROWS][LV_W], s2[ROWS][LV_W];
     __shared__ double s_inv[WIN * WIN + 1];  // reciprocals of the window's pixel counts
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (threadIdx.x <= WIN * WIN) s_inv[threadIdx.x] = 1.0 / max((int)threadIdx.x, 1);
-    const int bx = blockIdx.x * LV_W, by = blockIdx.y * 4 * R, x = bx + lane;
+    for (int i = threadIdx.x; i <= WIN * WIN; i += 64 * NW) s_inv[i] = 1.0 / max(i, 1);
+    const int bx = blockIdx.x * LV_W, by = blockIdx.y * NW * R, x = bx + lane;
     const size_t plane = (size_t)H * W;
     const bool inside = bx >= HW && bx + LV_W + HW <= W;  // no lane's window leaves the image in x
     const int nx = max(min(x + HW, W - 1) - max(x - HW, 0) + 1, 1);
     double v[R];
 #pragma unroll
     for (int o = 0; o < R; ++o) v[o] = 0.0;
+#pragma unroll 1
     for (int c = 0; c < 3; ++c) {
         if (c) __syncthreads();  // the previous channel's sums are read
 #pragma unroll 2
-        for (int q = wave; q < ROWS; q += 4) {
+        for (int q = wave; q < ROWS; q += NW) {
             const int y = by - HW + q;
             float f[WIN];
 #pragma unroll
@@ -205,14 +209,14 @@ k_local_var(const float *__restrict__ img, int H, int W, double *__restrict__ lv
         lo = a < lo ? a : lo;
         hi = b > hi ? b : hi;
     }
-    __shared__ unsigned long long s_lo[4], s_hi[4];
+    __shared__ unsigned long long s_lo[NW], s_hi[NW];
     if (lane == 0) {
         s_lo[wave] = lo;
         s_hi[wave] = hi;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int w = 1; w < 4; ++w) {
+        for (int w = 1; w < NW; ++w) {
             lo = s_lo[w] < lo ? s_lo[w] : lo;
             hi = s_hi[w] > hi ? s_hi[w] : hi;
         }
@@ -570,19 +574,19 @@ struct SaLayout {
     size_t minmax, bmm, lv, gsum, bsum, total;
 };
 
-// Rows per wave of k_local_var: 8, or 2 (more rows of halo per output) where 8 would leave the
-// chip without two workgroups per compute unit.
+// Rows per workgroup of k_local_var: 32, or 8 (more rows of halo per output) where 32 would leave
+// the chip without two workgroups per compute unit.
 int lv_rows(int H, int W)
 {
     const long long wgs = (long long)((W + LV_W - 1) / LV_W) * ((H + 31) / 32);
-    return wgs >= 512 ? 8 : 2;
+    return wgs >= 512 ? 32 : 8;
 }
 
 SaLayout sa_layout(long long npix, int H, int W)
 {
     SaLayout L;
     const long long nb = (npix + NLV_BLOCK - 1) / NLV_BLOCK;
-    const int rows = 4 * lv_rows(H, W);
+    const int rows = lv_rows(H, W);
     const long long nblk = (long long)((W + LV_W - 1) / LV_W) * ((H + rows - 1) / rows);
     L.minmax = 0;
     L.bmm = up256(16);
@@ -594,21 +598,21 @@ SaLayout sa_layout(long long npix, int H, int W)
     return L;
 }
 
-template <int R>
-void launch_local_var(hipStream_t st, const dim3 &grid, const float *img, int H, int W, int h,
-                      double *lv, unsigned long long *bmm)
+// HW: the build whose window half width is h.
+template <int HW = 0>
+void launch_local_var(hipStream_t st, const dim3 &grid, int rows, const float *img, int H, int W,
+                      int h, double *lv, unsigned long long *bmm)
 {
-    auto run = [&](auto kern) { kern<<<grid, 256, 0, st>>>(img, H, W, lv, bmm); };
-    switch (h) {
-    case 0: run(k_local_var<0, R>); break;
-    case 1: run(k_local_var<1, R>); break;
-    case 2: run(k_local_var<2, R>); break;
-    case 3: run(k_local_var<3, R>); break;
-    case 4: run(k_local_var<4, R>); break;
-    case 5: run(k_local_var<5, R>); break;
-    case 6: run(k_local_var<6, R>); break;
-    default: run(k_local_var<7, R>); break;
+    if (h != HW) {
+        if constexpr (HW < LV_HMAX)
+            launch_local_var<HW + 1>(st, grid, rows, img, H, W, h, lv, bmm);
+        return;
     }
+    // 32 rows as 8 waves of 4, or 4 of 8 for windows of 13 and 15, whose waves read many more rows
+    // than they share (7 x 7 at 2048 x 2048: 80 and 88 us for the start; 15 x 15: 164 and 153)
+    constexpr int R = HW < 6 ? 4 : 8, NW = 32 / R;
+    if (rows == 32) k_local_var<HW, R, NW><<<grid, 64 * NW, 0, st>>>(img, H, W, lv, bmm);
+    else k_local_var<HW, 2, 4><<<grid, 256, 0, st>>>(img, H, W, lv, bmm);
 }
 
 int launched() { return hipGetLastError() == hipSuccess ? DBMP_OK : DBMP_EHIP; }
@@ -690,9 +694,8 @@ int dbmp_sa_init(dbmp_aids_stream stream, const float *target, int H, int W, int
     auto *bsum = (long long *)(ws + L.bsum);
     hipStream_t st = (hipStream_t)stream;
     const int rows = lv_rows(H, W);
-    const dim3 lvg((W + LV_W - 1) / LV_W, (H + 4 * rows - 1) / (4 * rows));
-    if (rows == 8) launch_local_var<8>(st, lvg, target, H, W, win / 2, lv, bmm);
-    else launch_local_var<2>(st, lvg, target, H, W, win / 2, lv, bmm);
+    const dim3 lvg((W + LV_W - 1) / LV_W, (H + rows - 1) / rows);
+    launch_local_var(st, lvg, rows, target, H, W, win / 2, lv, bmm);
     int nslots = (int)(lvg.x * lvg.y);
     if (nslots > 2048) {  // too many for every workgroup of k_nlv to read
         k_lv_minmax<<<1, 1024, 0, st>>>(bmm, nslots, minmax);
