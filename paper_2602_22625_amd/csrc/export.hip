@@ -148,28 +148,43 @@ __device__ __forceinline__ LayerMap layer_map(const float *p, int Hb, int Wb, fl
     return m;
 }
 
+// The integer nearest zero, saturated to the range of int (a cast leaves that undefined).
+__device__ __forceinline__ int sat_int(double x)
+{
+    int i;
+    asm("v_cvt_i32_f64 %0, %1" : "=v"(i) : "v"(x));
+    return i;
+}
+
+constexpr int EXPORT_THREADS = 256;
+
 // One workgroup per primitive: the primitive's constants once (by one wave, while the others copy
 // the bitmap), then its box's pixels in row-major order, 256 at a time (coalesced stores into its
 // packed box; the row and column advance by a fixed step, no division).
 // LDS: the bitmap is first copied to LDS inside a border of zeros, if the box has at least half as
 // many values as the bitmap texels: 64 neighbouring pixels read texels of some 40 cache lines, and
 // the L1 serves one line per clock, so four loads per value from memory cost about 160 clocks per
-// 64 values (271 us for 54 million values at 1024 x 1024 x 2, 8,192 primitives, 64 x 64 float32
-// bitmaps), LDS reads with their bank conflicts about 30 (145 us: now bound by the float64
-// coordinates' instructions; 217 MB are written, 43 us). Smaller boxes read from memory.
+// 64 values. Bound by instructions (82 % of the issue slots, 42 per value of which 14 in float64),
+// so the loop over the copy has no comparisons: a position outside is moved to a cell of zeros, and
+// the pixel's place in the box is mapped straight to the bitmap. 54 million values at 1024 x 1024
+// x 2, 8,192 primitives, 64 x 64 float32 bitmaps: 271 us from memory, 145 with the comparisons (four
+// values at a time or 512 threads were no faster), 108 now; 217 MB are written, 43 us. Smaller boxes
+// read from memory.
 // (A grid of (primitive, tile row, tile column) sized by the largest box launched mostly empty
 // workgroups: 5.1 ms at 2048 x 2048 with 65,536 primitives against 0.59 ms; one wave per primitive
 // took 1.17 ms: the largest boxes then run on 64 lanes.)
 template <typename TexT, bool LDS>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(EXPORT_THREADS)
 k_export_layers(const float *__restrict__ params, const int *__restrict__ idx, int B,
                 const TexT *__restrict__ atlas, int Hb, int Wb, int pitch, double rho,
                 float alpha_max, const int4 *__restrict__ boxes,
                 const long long *__restrict__ offsets, float *__restrict__ alpha_out,
                 float *__restrict__ colour_out)
 {
+    constexpr int NT = EXPORT_THREADS;
     extern __shared__ __attribute__((aligned(16))) char s_raw[];
     __shared__ LayerMap s_map;
+    __shared__ int s_fin;  // the map's constants are finite
     TexT *s_tex = reinterpret_cast<TexT *>(s_raw);
     const int i = blockIdx.x;
     const int4 box = boxes[i];
@@ -182,60 +197,90 @@ k_export_layers(const float *__restrict__ params, const int *__restrict__ idx, i
     float *out = alpha_out + offsets[i];
     const int k = idx[i];
     if (!(k >= 0 && k < B)) {
-        for (int j = threadIdx.x; j < n; j += 256) out[j] = 0.f;
+        for (int j = threadIdx.x; j < n; j += NT) out[j] = 0.f;
         return;
     }
     const TexT *bm = atlas + (size_t)k * Hb * Wb;
     const bool staged = LDS && 2LL * n >= (long long)Hb * Wb;
     if (wave == 0) {
+        if (LDS && staged) {  // the border: rows -1, Hb, Hb + 1 and columns -1, Wb, Wb + 1
+            for (int x = lane; x < Wb + 3; x += 64)
+                s_tex[x] = s_tex[(Hb + 1) * pitch + x] = s_tex[(Hb + 2) * pitch + x] = TexT(0);
+            for (int y = lane; y < Hb; y += 64) {
+                TexT *t = s_tex + (y + 1) * pitch;
+                t[0] = t[Wb + 1] = t[Wb + 2] = TexT(0);
+            }
+        }
         const LayerMap m = layer_map(p, Hb, Wb, alpha_max);
-        if (lane == 0) s_map = m;
-    }
-    if (LDS && staged) {  // rows -1 .. Hb, columns -1 .. Wb; the map's wave takes fewer
-        for (int y = wave == 0 ? 3 : wave - 1; y < Hb + 2; y += 4)
-            for (int x = lane; x < Wb + 2; x += 64)
-                s_tex[y * pitch + x] = y >= 1 && y <= Hb && x >= 1 && x <= Wb
-                                           ? bm[(size_t)(y - 1) * Wb + x - 1] : TexT(0);
+        if (lane == 0) {
+            s_map = m;
+            s_fin = isfinite(m.aU) && isfinite(m.bU) && isfinite(m.eU) && isfinite(m.aV) &&
+                    isfinite(m.bV) && isfinite(m.eV) && isfinite(m.ka);
+        }
+    } else if (LDS && staged) {
+#pragma unroll 4
+        for (int y = wave - 1; y < Hb; y += NT / 64 - 1)
+            for (int x = lane; x < Wb; x += 64)
+                s_tex[(y + 1) * pitch + x + 1] = bm[(size_t)y * Wb + x];
     }
     __syncthreads();
     const LayerMap m = s_map;
     const double x0 = box.x + 0.5, y0 = box.y + 0.5, ir = 1.0 / rho;
-    const int step_y = 256 / bw, step_x = 256 - step_y * bw;
+    const int step_y = NT / bw, step_x = NT - step_y * bw;
     int by = (int)threadIdx.x / bw, bx = (int)threadIdx.x - by * bw;
-    for (int j = threadIdx.x; j < n; j += 256) {
-        float a = 0.f;
-        // canvas point of export pixel (X, Y): (X + 0.5) / rho - 0.5
-        const double x = fma(x0 + bx, ir, -0.5), y = fma(y0 + by, ir, -0.5);
-        const double U = fma(m.aU, x, fma(m.bU, y, m.eU));
-        const double V = fma(m.aV, x, fma(m.bV, y, m.eV));
-        const double u0 = floor(U), v0 = floor(V);
-        if (u0 >= -1.0 && u0 <= Wb - 1.0 && v0 >= -1.0 && v0 <= Hb - 1.0) {
-            const int iu = (int)u0, iv = (int)v0;
-            const float wu = (float)(U - u0), wv = (float)(V - v0);
-            float p00, p01, p10, p11;
-            if (LDS && staged) {
-                const TexT *t = s_tex + (iv + 1) * pitch + iu + 1;
-                p00 = texel<TexT>(t[0]);
-                p01 = texel<TexT>(t[1]);
-                p10 = texel<TexT>(t[pitch]);
-                p11 = texel<TexT>(t[pitch + 1]);
-            } else {
-                p00 = tex_at(bm, Hb, Wb, iv, iu);
-                p01 = tex_at(bm, Hb, Wb, iv, iu + 1);
-                p10 = tex_at(bm, Hb, Wb, iv + 1, iu);
-                p11 = tex_at(bm, Hb, Wb, iv + 1, iu + 1);
-            }
-            const float top = fmaf(wu, p01 - p00, p00), bot = fmaf(wu, p11 - p10, p10);
-            const float M = fmaf(wv, bot - top, top);
-            a = m.ka * M;
-        }
-        out[j] = a;
+    auto next = [&] {
         bx += step_x;
         by += step_y;
         if (bx >= bw) {
             bx -= bw;
             ++by;
         }
+    };
+    // canvas point of export pixel (X, Y): (X + 0.5) / rho - 0.5
+    auto coords = [&](double &U, double &V) {
+        const double x = fma(x0 + bx, ir, -0.5), y = fma(y0 + by, ir, -0.5);
+        U = fma(m.aU, x, fma(m.bU, y, m.eU));
+        V = fma(m.aV, x, fma(m.bV, y, m.eV));
+    };
+    auto inside = [&](double u0, double v0) {
+        return u0 >= -1.0 && u0 <= Wb - 1.0 && v0 >= -1.0 && v0 <= Hb - 1.0;
+    };
+    auto value = [&](float wu, float wv, float p00, float p01, float p10, float p11) {
+        const float top = fmaf(wu, p01 - p00, p00), bot = fmaf(wu, p11 - p10, p10);
+        return m.ka * fmaf(wv, bot - top, top);
+    };
+    if (LDS && staged && s_fin) {
+        // bitmap coordinates as a function of the pixel's place in the box
+        const double AU = m.aU * ir, BU = m.bU * ir, AV = m.aV * ir, BV = m.bV * ir;
+        const double ex = fma(x0, ir, -0.5), ey = fma(y0, ir, -0.5);
+        const double EU = fma(m.aU, ex, fma(m.bU, ey, m.eU)), EV = fma(m.aV, ex, fma(m.bV, ey, m.eV));
+        for (int j = threadIdx.x; j < n; j += NT) {
+            const double U = fma(AU, (double)bx, fma(BU, (double)by, EU));
+            const double V = fma(AV, (double)bx, fma(BV, (double)by, EV));
+            const double u0 = floor(U), v0 = floor(V);
+            // outside the bitmap and its border (as unsigned: past the end) lies a cell of zeros
+            const unsigned iu = min((unsigned)sat_int(u0) + 1u, (unsigned)Wb + 1u);
+            const unsigned iv = min((unsigned)sat_int(v0) + 1u, (unsigned)Hb + 1u);
+            const TexT *t = s_tex + __umul24(iv, pitch) + iu;
+            out[j] = value((float)(U - u0), (float)(V - v0), texel<TexT>(t[0]), texel<TexT>(t[1]),
+                           texel<TexT>(t[pitch]), texel<TexT>(t[pitch + 1]));
+            next();
+        }
+        return;
+    }
+    for (int j = threadIdx.x; j < n; j += NT) {
+        double U, V;
+        coords(U, V);
+        const double u0 = floor(U), v0 = floor(V);
+        float a = 0.f;
+        if (inside(u0, v0)) {
+            const int iu = (int)u0, iv = (int)v0;
+            a = value((float)(U - u0), (float)(V - v0), tex_at(bm, Hb, Wb, iv, iu),
+                      tex_at(bm, Hb, Wb, iv, iu + 1), tex_at(bm, Hb, Wb, iv + 1, iu),
+                      tex_at(bm, Hb, Wb, iv + 1, iu + 1));
+        }
+        out[j] = a;
+        next();
     }
 }
 
@@ -290,15 +335,15 @@ int dbmp_export_layers(dbmp_export_stream stream, const float *params, const int
     if (!params || !atlas_idx || !atlas || !boxes || !offsets || !colour_out) return DBMP_EINVAL;
     if (max_w > 0 && !alpha_out) return DBMP_EINVAL;
     hipStream_t st = (hipStream_t)stream;
-    // bitmaps in LDS up to 40 KB with their border (four workgroups per compute unit); an odd
-    // pitch in 4-byte words spreads a column over the banks
+    // bitmaps in LDS up to 42 KB with their border (three or more workgroups per compute unit); an
+    // odd pitch in 4-byte words spreads a column over the banks
     const int esz = atlas_dtype == DBMP_F32 ? 4 : 2;
-    const int pitch = ((Wb + 2) * esz / 4 | 1) * (4 / esz) + (esz == 2 && (Wb & 1) ? 2 : 0);
-    const long long lds = (long long)(Hb + 2) * pitch * esz;
-    const bool stage = lds <= 40 * 1024;
+    const int pitch = (((Wb + 3) * esz + 3) / 4 | 1) * (4 / esz);
+    const long long lds = (long long)(Hb + 3) * pitch * esz;
+    const bool stage = lds <= 42 * 1024;
     auto run = [&](auto texel_of, auto kern) {
         using TexT = decltype(texel_of);
-        kern<<<N, 256, stage ? (size_t)lds : 0, st>>>(
+        kern<<<N, EXPORT_THREADS, stage ? (size_t)lds : 0, st>>>(
             params, atlas_idx, B, (const TexT *)atlas, Hb, Wb, pitch, rho, alpha_max,
             (const int4 *)boxes, offsets, alpha_out, colour_out);
     };
