@@ -2,8 +2,9 @@
 // MLP head) that maps a target image to primitive parameters. Training and inference run here,
 // in bfloat16 with float32 accumulation on the matrix cores of gfx950 (v_mfma_f32_16x16x32_bf16).
 //
-// Every layer is one matrix product C[M][N] = sum_k A(m, k) B(k, n), computed by one tiled
-// kernel whose operands are produced by gather functors:
+// The layers of the usual shapes run on the kernels of conv.hip and wgrad.hip. Any other is one
+// matrix product C[M][N] = sum_k A(m, k) B(k, n), computed here by one tiled kernel whose operands
+// are produced by gather functors:
 //   convolution forward      M = output pixels (b, oy, ox), N = out channels, K = (ky, kx, ic):
 //                            A = the image patch under the filter (implicit im2col), B = W;
 //   convolution grad-input   one product per parity class of input pixels (y % 2, x % 2):
