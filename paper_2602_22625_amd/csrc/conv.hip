@@ -438,7 +438,8 @@ void launch(const ConvArgs &a, hipStream_t st)
 // where that leaves 1,024 waves (64 x 32 x 32 x 128 -> 256: forward 16.0 us with 2 x 4, 25.3 with
 // 1 x 4; input gradient 26.6 against 30.8), else 1 x 4 (64 x 16 x 16 x 256 -> 256: 11.4 against 18.0
 // with 2 x 4, 15.8 with 1 x 1), else the smallest (64 x 8 x 8 x 256 -> 256: 5.9 against 10.9 with
-// 1 x 4). 4 x 4 was no faster anywhere.
+// 1 x 4). 4 x 4 was no faster anywhere, nor 2 x 2 for 32 channels (64 x 128 x 128 x 32 <- 64, input
+// gradient: 53 us, 46 with 1 x 2).
 template <int MODE, int NCH>
 void launch_mn(const ConvArgs &a, hipStream_t st)
 {
