@@ -337,7 +337,16 @@ k_prep(const float *params, const int *__restrict__ idx, long long n_rows,
         b = find_image(n_images, (long long)blockIdx.x * PREP_PRIMS,
                        [&](int i) { return imgs[i].prim_off; });
     if (threadIdx.x < PREP_PRIMS && g_rec < n_rows) {
-        while (b + 1 < n_images && imgs[b + 1].prim_off <= g_rec) ++b;
+        // from the workgroup's first image on in doubling steps, then halving: usually one look at
+        // the next image, and a few where a workgroup's rows belong to many images (or span many
+        // empty ones)
+        int step = 1;
+        while (step < n_images - b && imgs[b + step].prim_off <= g_rec) {
+            b += step;
+            step <<= 1;
+        }
+        while ((step >>= 1) > 0)
+            if (step < n_images - b && imgs[b + step].prim_off <= g_rec) b += step;
         D = imgs[b];
         k = idx[g_rec];
         k_ok = k >= 0 && k < B;
