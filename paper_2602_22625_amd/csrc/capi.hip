@@ -1,16 +1,17 @@
 // C ABI of the rasteriser (declared in include/diffbmp.h): context, workspace and launches.
 #include "dbmp_internal.h"
 #include "diffbmp.h"
+#include "flag_slots.h"
 #include "workspace.h"
 
 #include <limits.h>
 #include <stdio.h>
 
 #include <algorithm>
+#include <map>
 #include <new>
 #include <string>
 #include <vector>
-
 
 using namespace dbmp;
 
@@ -23,9 +24,8 @@ struct dbmp_ctx {
     std::string err;
     Buf recs, tile_count, tile_len, lists, saveK, saveT, atlas_pad, box, imgs, counter,
         list_max, loss_tile, order, order_hist, queue;
-    volatile int *flags = nullptr;  // F_COUNT slots in pinned host memory, written by the device
-    int *flags_dev = nullptr;       // their device address
-    int list_cap = 0;               // entries per tile list
+    FlagSlot flags;    // F_COUNT words in pinned host memory, written by the device
+    int list_cap = 0;  // entries per tile list
     // launch schedule of the raster kernels (dbmp_set_schedule)
     int sched = SCHED_GRID;
     int wgs_per_cu = 4;
@@ -106,6 +106,34 @@ struct HipOps {
         return e == hipSuccess ? 0 : hip_fail(c, e, "workspace clear");
     }
 };
+
+// Pinned memory of the contexts' flags (flag_slots.h), on the current device. Coherent: the device's
+// stores reach the host's memory, and nothing of it stays in the device's caches.
+struct PinnedOps {
+    int acquire(void **p, size_t bytes)
+    {
+        if (hipHostMalloc(p, bytes, hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess)
+            return 0;
+        (void)hipGetLastError();
+        return DBMP_ENOMEM;
+    }
+    void release(void *p) { (void)hipHostFree(p); }
+    bool device_address(void *p, void **d)
+    {
+        if (hipHostGetDevicePointer(d, p, 0) == hipSuccess) return true;
+        (void)hipGetLastError();
+        return false;
+    }
+};
+
+// A device's slots. Never destroyed: a context may be given back while the process ends.
+FlagSlots &flag_slots(int device)
+{
+    static std::mutex *mu = new std::mutex;
+    static auto *pools = new std::map<int, FlagSlots>;
+    std::lock_guard<std::mutex> lk(*mu);
+    return (*pools)[device];
+}
 
 // Grows `b` to at least `bytes` (contents not preserved; must_be_zero: the new block is cleared).
 // Synchronous; refused while the stream is being captured into a graph. A growth frees the old
@@ -279,7 +307,7 @@ int render_impl(dbmp_ctx *c, hipStream_t st, const std::vector<dbmp_image_desc> 
     ba.alpha_max = alpha_max; ba.TS = tile; ba.atlas_pad = c->atlas_pad.p;
     ba.box = (int *)c->box.p; ba.recs = (PrimRec *)c->recs.p;
     ba.tile_count = (int *)c->tile_count.p; ba.lists = (int *)c->lists.p;
-    ba.list_cap = c->list_cap; ba.flags = c->flags_dev; ba.pad_atlas = false;
+    ba.list_cap = c->list_cap; ba.flags = c->flags.dev; ba.pad_atlas = false;
     ba.order = c->sched != SCHED_GRID ? (int *)c->order.p : nullptr;
     ba.order_hist = (int *)c->order_hist.p;
     ba.adam = fuse.adam;
@@ -306,7 +334,7 @@ int render_impl(dbmp_ctx *c, hipStream_t st, const std::vector<dbmp_image_desc> 
     }
     ra.bg = bg; ra.bg_pp = bg_pp; ra.image = image; ra.alpha = alpha;
     ra.saveK = (int *)c->saveK.p; ra.saveT = (float *)c->saveT.p;
-    ra.flags = c->flags_dev; ra.TS = tile;
+    ra.flags = c->flags.dev; ra.TS = tile;
     ra.pair_counter = (unsigned long long *)c->counter.p;
     ra.loss_tile = (float *)c->loss_tile.p;
     ra.sched = c->sched;
@@ -358,16 +386,17 @@ int dbmp_create(dbmp_ctx **out, int device, long long list_capacity)
     c->device = device;
     c->list_cap = round_cap(list_capacity > 0 ? (int)list_capacity : 256);
     DeviceGuard g(device);
-    void *fl = nullptr, *fd = nullptr;
-    if (hipHostMalloc(&fl, 4 * F_COUNT, hipHostMallocMapped) != hipSuccess) {
-        delete c;
-        return DBMP_ENOMEM;
+    int rc = DBMP_ENOMEM;
+    try {
+        PinnedOps pinned;
+        rc = flag_slots(device).take(&c->flags, pinned);
+    } catch (const std::bad_alloc &) {
     }
-    c->flags = (volatile int *)fl;
-    for (int i = 0; i < F_COUNT; ++i) c->flags[i] = 0;
-    if (hipHostGetDevicePointer(&fd, fl, 0) != hipSuccess) { dbmp_destroy(c); return DBMP_EHIP; }
-    c->flags_dev = (int *)fd;
-    int rc = ensure(c, c->counter, 8 * DBMP_COUNTER_SLOTS, nullptr, "counter");
+    if (rc) {
+        delete c;
+        return rc == FlagSlots::NO_ADDRESS ? DBMP_EHIP : rc;
+    }
+    rc = ensure(c, c->counter, 8 * DBMP_COUNTER_SLOTS, nullptr, "counter");
     if (!rc) rc = ensure(c, c->list_max, 4 * DBMP_COUNTER_SLOTS, nullptr, "list_max");
     if (!rc) rc = ensure(c, c->queue, 16, nullptr, "work queues");
     if (rc) { dbmp_destroy(c); return rc; }
@@ -395,7 +424,8 @@ int dbmp_destroy(dbmp_ctx *c)
                      &c->loss_tile, &c->order, &c->order_hist, &c->queue};
         for (Buf *b : bs)
             if (b->p) (void)hipFree(b->p);
-        if (c->flags) (void)hipHostFree((void *)c->flags);
+        PinnedOps pinned;
+        flag_slots(c->device).give(&c->flags, pinned);
     }
     delete c;
     return DBMP_OK;
@@ -652,8 +682,9 @@ int dbmp_check(dbmp_ctx *c, dbmp_stream stream)
     hipError_t e = hipStreamSynchronize((hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(c, e, "hipStreamSynchronize");
     int f[F_COUNT];
+    volatile int *fl = c->flags.host;
     for (int i = 0; i < F_COUNT; ++i)
-        if ((f[i] = c->flags[i]) != 0) c->flags[i] = 0;
+        if ((f[i] = fl[i]) != 0) fl[i] = 0;
     if (f[F_S_OVERFLOW])
         return fail(c, DBMP_EOVERFLOW, "a tile list exceeds the capacity of " +
                                            std::to_string(c->list_cap) +
