@@ -302,7 +302,8 @@ int dbmp_fit_step_batched(dbmp_ctx *ctx, dbmp_stream stream, int n_images,
                           float *image, float *grad, float *m, float *v, int32_t *state, float lr,
                           float beta1, float beta2, float eps);
 
-/* Synchronises `stream` and reports the device-side errors raised by any forward since the
+/* Synchronises `stream`, and the device's streams that synchronise with the null stream (created
+ * without hipStreamNonBlocking), and reports the device-side errors raised by any forward since the
  * previous dbmp_check: DBMP_EOVERFLOW (a tile list did not fit; that forward's image is not
  * valid), DBMP_EINVAL (atlas index out of range), DBMP_ENONFINITE, or DBMP_OK. The reported
  * errors are cleared. */

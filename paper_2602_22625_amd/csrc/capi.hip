@@ -680,11 +680,14 @@ int dbmp_check(dbmp_ctx *c, dbmp_stream stream)
     if (!c) return DBMP_EINVAL;
     DeviceGuard g(c->device);
     hipError_t e = hipStreamSynchronize((hipStream_t)stream);
+    // The context's forwards may be on other streams too (a graph replayed elsewhere): those that
+    // synchronise with the null stream are waited for, as a copy of the flags from device memory did.
+    if (e == hipSuccess && stream) e = hipStreamSynchronize(nullptr);
     if (e != hipSuccess) return hip_fail(c, e, "hipStreamSynchronize");
+    // read and cleared in one step: an error raised meanwhile by a forward still running is kept
     int f[F_COUNT];
-    volatile int *fl = c->flags.host;
     for (int i = 0; i < F_COUNT; ++i)
-        if ((f[i] = fl[i]) != 0) fl[i] = 0;
+        f[i] = __atomic_exchange_n(&c->flags.host[i], 0, __ATOMIC_ACQ_REL);
     if (f[F_S_OVERFLOW])
         return fail(c, DBMP_EOVERFLOW, "a tile list exceeds the capacity of " +
                                            std::to_string(c->list_cap) +
