@@ -18,11 +18,19 @@
 namespace dbmp {
 namespace {
 
+// A box as the caller's int32 [N, 4] holds it: one 16-byte access, at any 4-byte address.
+typedef int BoxWords __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ int4 box_at(const BoxWords *__restrict__ boxes, long long i)
+{
+    const BoxWords b = boxes[i];
+    return make_int4(b.x, b.y, b.z, b.w);
+}
+
 // Canvas point of export pixel X: (X + 0.5) / rho - 0.5; export coordinate of canvas point x:
 // rho (x + 0.5) - 0.5.
 __global__ void __launch_bounds__(256)
 k_export_boxes(const float *__restrict__ params, int N, int Hb, int Wb, int HH, int WW,
-               double rho, int4 *__restrict__ boxes)
+               double rho, BoxWords *__restrict__ boxes)
 {
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= N) return;
@@ -52,7 +60,7 @@ k_export_boxes(const float *__restrict__ params, int N, int Hb, int Wb, int HH, 
             w = (int)(fx1 - fx0) + 1; h = (int)(fy1 - fy0) + 1;
         }
     }
-    boxes[i] = make_int4(x0, y0, w, h);
+    boxes[i] = BoxWords{x0, y0, w, h};
 }
 
 // Exclusive scan of the N areas into offsets[0 .. N], and the largest box, by one workgroup of 1024
@@ -62,7 +70,7 @@ k_export_boxes(const float *__restrict__ params, int N, int Hb, int Wb, int HH, 
 constexpr int OFF_PER = 8;
 
 __global__ void __launch_bounds__(1024)
-k_export_offsets(const int4 *__restrict__ boxes, long long *__restrict__ off, int N,
+k_export_offsets(const BoxWords *__restrict__ boxes, long long *__restrict__ off, int N,
                  int *__restrict__ max_wh)
 {
     __shared__ long long wsum[16];
@@ -76,7 +84,7 @@ k_export_offsets(const int4 *__restrict__ boxes, long long *__restrict__ off, in
 #pragma unroll
         for (int k = 0; k < OFF_PER; ++k) {
             const int i = i0 + k;
-            const int4 bx = i < N ? boxes[i] : make_int4(0, 0, 0, 0);
+            const int4 bx = i < N ? box_at(boxes, i) : make_int4(0, 0, 0, 0);
             w = max(w, bx.z);
             h = max(h, bx.w);
             v[k] = run;
@@ -286,7 +294,7 @@ struct LayerArgs {
 template <typename TexT, bool LDS, int NT>
 __global__ void __launch_bounds__(NT)
 k_export_layers(LayerArgs a, const TexT *__restrict__ atlas, const float *__restrict__ params,
-                const int *__restrict__ idx, const int4 *__restrict__ boxes,
+                const int *__restrict__ idx, const BoxWords *__restrict__ boxes,
                 const long long *__restrict__ offsets, float *__restrict__ alpha_out,
                 float *__restrict__ colour_out)
 {
@@ -295,7 +303,7 @@ k_export_layers(LayerArgs a, const TexT *__restrict__ atlas, const float *__rest
     __shared__ int s_fin;  // the map's constants are finite
     TexT *s_tex = reinterpret_cast<TexT *>(s_raw);
     const int i = blockIdx.x;
-    const int4 box = boxes[i];
+    const int4 box = box_at(boxes, i);
     const int n = box.z * box.w;
     const float *p = params + (size_t)i * 8;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -338,7 +346,7 @@ k_export_layers(LayerArgs a, const TexT *__restrict__ atlas, const float *__rest
 template <typename TexT, bool LDS, int NT>
 __global__ void __launch_bounds__(NT, 8)
 k_export_chunks(LayerArgs a, const TexT *__restrict__ atlas, const float *__restrict__ params,
-                const int *__restrict__ idx, const int4 *__restrict__ boxes,
+                const int *__restrict__ idx, const BoxWords *__restrict__ boxes,
                 const long long *__restrict__ offsets, float *__restrict__ alpha_out,
                 float *__restrict__ colour_out)
 {
@@ -364,7 +372,7 @@ k_export_chunks(LayerArgs a, const TexT *__restrict__ atlas, const float *__rest
                 for (int q = 0; q < 5; ++q) p[q] = params[8 * prim(lane) + q];
                 s_off[lane] = offsets[prim(lane)];
             }
-            box = boxes[prim(lane)];
+            box = box_at(boxes, prim(lane));
             k = idx[prim(lane)];
         }
         const int n = box.z * box.w;
@@ -456,8 +464,8 @@ int dbmp_export_boxes(dbmp_export_stream stream, const float *params, int N, int
     hipStream_t st = (hipStream_t)stream;
     if (N > 0)
         k_export_boxes<<<(N + 255) / 256, 256, 0, st>>>(params, N, Hb, Wb, HH, WW, rho,
-                                                       (int4 *)boxes);
-    k_export_offsets<<<1, 1024, 0, st>>>((const int4 *)boxes, offsets, N, max_wh);
+                                                       (BoxWords *)boxes);
+    k_export_offsets<<<1, 1024, 0, st>>>((const BoxWords *)boxes, offsets, N, max_wh);
     return launched();
 }
 
@@ -499,7 +507,7 @@ int dbmp_export_layers(dbmp_export_stream stream, const float *params, const int
         const unsigned grid = (unsigned)(N / chunk + (N % chunk != 0));
         auto go = [&](auto kern) {
             kern<<<grid, threads, stage ? (size_t)lds : 0, st>>>(
-                a, (const TexT *)atlas, params, atlas_idx, (const int4 *)boxes, offsets, alpha_out,
+                a, (const TexT *)atlas, params, atlas_idx, (const BoxWords *)boxes, offsets, alpha_out,
                 colour_out);
         };
         if (chunk == 1) go(one);
