@@ -473,9 +473,12 @@ __global__ void __launch_bounds__(256) k_colsum(const u16 *__restrict__ z, int M
 static hipError_t colsum(hipStream_t st, const u16 *dz, int M, int N, float *db)
 {
     if (N % 8 == 0 && N <= 2048 && ((uintptr_t)dz & 15) == 0) {
-        // up to 256 workgroups of at least 8 passes over their rows (2,048 rows per workgroup left
-        // the head's 1,024 rows to one: 36 us for N = 512, 6 us now)
-        const int rows = std::max(8 * 4 * (256 / (N >> 3)), (M + 255) / 256);
+        // 8 passes over its rows per workgroup (2,048 rows at most: 5.9 us for 65,536 x 8, 8.0 with
+        // 8,192), but no more than 256 workgroups, whose atomics meet on each column, or 512 above
+        // 200 MB, where more loads in flight count (1,048,576 x 264: 90 us, 129 with 256; 65,536 x
+        // 512: 22 us, 17 with 256). 1,024 x 512: 5 us, 25 with 2,048 rows each.
+        const int most = (long long)M * N > 100000000 ? 512 : 256;
+        const int rows = std::max(std::min(2048, 8 * 4 * (256 / (N >> 3))), M / most + (M % most != 0));
         k_colsum8<<<(M + rows - 1) / rows, 256, 0, st>>>(dz, M, N, rows, db);
     } else {
         const int rows = 4096;
