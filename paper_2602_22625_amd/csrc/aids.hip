@@ -21,7 +21,11 @@ namespace {
 // x into a second LDS buffer, then along y into the output. Waves take rows, lanes columns: no
 // division. Bands are short where that fills the chip (a 64 x 128 x 128 atlas, 16 rows: 512
 // workgroups): bands as tall as LDS holds left one workgroup per compute unit, and each of its
-// threads 24 pixels of dependent LDS reads: 33 us for a 64 x 128 x 128 bfloat16 atlas, 10 us now.
+// threads 24 pixels of dependent LDS reads: 33 us for a 64 x 128 x 128 bfloat16 atlas, 10 us now. They
+// are cut evenly and never taller than the bitmap (1,024 x 128 x 128 float32: 97 us cut into
+// 42, 42, 42 and 2 rows, 62 into four of 32; 4,096 x 32 x 32 at radius 15: 197 us as bands of 64 rows,
+// 72 as 32).
+// Bitmaps of up to 32 columns give a wave several rows (60,000 of 8 x 8: 224 us with one, 32 now).
 // ------------------------------------------------------------------------------------------
 constexpr int BLUR_RMAX = 16;
 constexpr int BLUR_LDS_BYTES = 48 * 1024;
@@ -47,29 +51,35 @@ template <> __device__ __forceinline__ _Float16 from_f32<_Float16>(float v)
 
 // RAD > 0: the radius at compile time (3 is sigma = 1, the method's), so that a pixel's LDS reads
 // are all in flight; 0: t.r.
-template <typename TexT, int RAD>
+template <typename TexT, int RAD, bool NARROW>
 __global__ void __launch_bounds__(256)
-k_blur(const TexT *__restrict__ in, TexT *__restrict__ out, int Hb, int Wb, int band, BlurTaps t)
+k_blur(const TexT *__restrict__ in, TexT *__restrict__ out, int Hb, int Wb, int band, int lg_,
+       BlurTaps t)
 {
     extern __shared__ float sh[];
     const int r = RAD ? RAD : t.r;
     const int b = blockIdx.y, y0 = blockIdx.x * band, rows = band + 2 * r;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, pitch = Wb + 2 * r;
+    const int pitch = Wb + 2 * r;
+    // a wave takes 1 << (6 - lg) rows of 1 << lg columns: of bitmaps of up to 32 columns (NARROW),
+    // several rows
+    const int lg = NARROW ? lg_ : 6;
+    const int row0 = (int)threadIdx.x >> lg, col0 = (int)threadIdx.x & ((1 << lg) - 1);
+    const int nrow = 256 >> lg, ncol = 1 << lg;
     float *raw = sh;                  // rows y0 - r .. y0 + band + r - 1 (zero outside the bitmap)
     float *hor = sh + rows * pitch;   // the same rows blurred along x
     const TexT *src = in + (size_t)b * Hb * Wb;
-    for (int y = wave; y < rows; y += 4) {
+    for (int y = row0; y < rows; y += nrow) {
         const int yy = y0 - r + y;
         const bool in_y = yy >= 0 && yy < Hb;
-        for (int x = lane; x < pitch; x += 64) {
+        for (int x = col0; x < pitch; x += ncol) {
             const int xx = x - r;
             raw[y * pitch + x] =
                 in_y && xx >= 0 && xx < Wb ? texel<TexT>(src[(size_t)yy * Wb + xx]) : 0.f;
         }
     }
     __syncthreads();
-    for (int y = wave; y < rows; y += 4)
-        for (int x = lane; x < Wb; x += 64) {
+    for (int y = row0; y < rows; y += nrow)
+        for (int x = col0; x < Wb; x += ncol) {
             const float *p = raw + y * pitch + x;
             float acc = 0.f;
             for (int d = 0; d <= 2 * r; ++d) acc = fmaf(t.w[d], p[d], acc);
@@ -77,8 +87,8 @@ k_blur(const TexT *__restrict__ in, TexT *__restrict__ out, int Hb, int Wb, int 
         }
     __syncthreads();
     TexT *dst = out + (size_t)b * Hb * Wb;
-    for (int y = wave; y < min(band, Hb - y0); y += 4)
-        for (int x = lane; x < Wb; x += 64) {
+    for (int y = row0; y < min(band, Hb - y0); y += nrow)
+        for (int x = col0; x < Wb; x += ncol) {
             const float *p = hor + y * Wb + x;
             float acc = 0.f;
             for (int d = 0; d <= 2 * r; ++d) acc = fmaf(t.w[d], p[d * Wb], acc);
@@ -642,23 +652,27 @@ int dbmp_blur_atlas(dbmp_aids_stream stream, const void *atlas, int B, int Hb, i
     double w[2 * BLUR_RMAX + 1], sum = 0.0;
     for (int d = -r; d <= r; ++d) sum += (w[d + r] = exp(-(double)d * d / (2.0 * sigma * sigma)));
     for (int d = -r; d <= r; ++d) t.w[d + r] = (float)(w[d + r] / sum);
-    // the sizes accepted are those whose band fits in 48 KB without the columns of zeros; with
-    // them a band needs at most 53 KB
+    // The sizes accepted are those of which a row fits in 48 KB without the columns of zeros; with
+    // them a band takes at most 60 KB (radius 16, 64 columns, 64 rows).
     int band = BLUR_LDS_BYTES / (8 * Wb) - 2 * r;
     if (band < 1) return DBMP_EINVAL;  // the band does not fit in LDS
     const long long fill = ((long long)B * Hb + 511) / 512;  // rows per workgroup of 512
-    band = (int)std::min<long long>(std::min(band, 64), std::max<long long>(fill, 8));
+    band = (int)std::min<long long>(std::min({band, 64, Hb}), std::max<long long>(fill, 8));
+    const int bands = (Hb + band - 1) / band;
+    band = (Hb + bands - 1) / bands;
+    int lg = 6;  // log2 of a wave's columns
+    while (lg > 0 && 1 << (lg - 1) >= Wb) --lg;
     const size_t lds = 4 * (size_t)(band + 2 * r) * (2 * Wb + 2 * r);
-    const dim3 grid((Hb + band - 1) / band, B);
+    const dim3 grid(bands, B);
     hipStream_t st = (hipStream_t)stream;
     auto run = [&](auto texel_of, auto kern) {
         using TexT = decltype(texel_of);
-        kern<<<grid, 256, lds, st>>>((const TexT *)atlas, (TexT *)out, Hb, Wb, band, t);
+        kern<<<grid, 256, lds, st>>>((const TexT *)atlas, (TexT *)out, Hb, Wb, band, lg, t);
     };
     auto run_r = [&](auto texel_of) {
         using TexT = decltype(texel_of);
-        if (r == 3) run(texel_of, k_blur<TexT, 3>);
-        else run(texel_of, k_blur<TexT, 0>);
+        if (lg < 6) run(texel_of, r == 3 ? k_blur<TexT, 3, true> : k_blur<TexT, 0, true>);
+        else run(texel_of, r == 3 ? k_blur<TexT, 3, false> : k_blur<TexT, 0, false>);
     };
     if (atlas_dtype == DBMP_F32) run_r(float{});
     else if (atlas_dtype == DBMP_F16) run_r(_Float16{});
