@@ -6,6 +6,7 @@
 #include "dbmp_aids.h"
 #include "dbmp_internal.h"
 #include "diffbmp.h"
+#include "sa_layout.h"
 
 #include <limits.h>
 #include <math.h>
@@ -99,10 +100,7 @@ k_blur(const TexT *__restrict__ in, TexT *__restrict__ out, int Hb, int Wb, int 
 // ------------------------------------------------------------------------------------------
 // Structure-aware initialisation (Sec. 3.2.2)
 // ------------------------------------------------------------------------------------------
-constexpr int LV_W = 64;        // output columns per workgroup
 constexpr int LV_HMAX = 7;      // largest window half-width (15 x 15)
-constexpr int NLV_BLOCK = 4096; // pixels per workgroup of k_nlv
-constexpr int NLV_GROUP = 64;   // pixels whose sampling weights are summed to one entry
 constexpr int BSUM_LDS = 2048;  // block totals the sampler scans in LDS
 
 // Ordering of non-negative doubles = ordering of their bit patterns as unsigned integers.
@@ -578,36 +576,6 @@ k_reinit(float *__restrict__ params, float *__restrict__ m, float *__restrict__ 
     if (count) atomicAdd(count, 1);
 }
 
-size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
-
-struct SaLayout {
-    size_t minmax, bmm, lv, gsum, bsum, total;
-};
-
-// Rows per workgroup of k_local_var: 32, or 8 (more rows of halo per output) where 32 would leave
-// the chip without two workgroups per compute unit.
-int lv_rows(int H, int W)
-{
-    const long long wgs = (long long)((W + LV_W - 1) / LV_W) * ((H + 31) / 32);
-    return wgs >= 512 ? 32 : 8;
-}
-
-SaLayout sa_layout(long long npix, int H, int W)
-{
-    SaLayout L;
-    const long long nb = (npix + NLV_BLOCK - 1) / NLV_BLOCK;
-    const int rows = lv_rows(H, W);
-    const long long nblk = (long long)((W + LV_W - 1) / LV_W) * ((H + rows - 1) / rows);
-    L.minmax = 0;
-    L.bmm = up256(16);
-    L.lv = L.bmm + up256(16 * (size_t)nblk);
-    L.gsum = L.lv + up256(8 * (size_t)npix);
-    L.bsum = L.gsum + up256(8 * 64 * (size_t)nb);
-    // never less than 16 bytes per pixel, the size that callers have always had to bring
-    L.total = std::max(L.bsum + up256(8 * (size_t)nb), L.gsum + up256(8 * (size_t)npix));
-    return L;
-}
-
 // HW: the build whose window half width is h.
 template <int HW = 0>
 void launch_local_var(hipStream_t st, const dim3 &grid, int rows, const float *img, int H, int W,
@@ -683,7 +651,7 @@ int dbmp_blur_atlas(dbmp_aids_stream stream, const void *atlas, int B, int Hb, i
 long long dbmp_sa_init_workspace_bytes(int H, int W)
 {
     if (H < 1 || W < 1 || (long long)H * W >= INT_MAX) return -1;
-    return (long long)sa_layout((long long)H * W, H, W).total;
+    return (long long)sa_layout(H, W).total;
 }
 
 int dbmp_sa_init(dbmp_aids_stream stream, const float *target, int H, int W, int win,
@@ -698,7 +666,7 @@ int dbmp_sa_init(dbmp_aids_stream stream, const float *target, int H, int W, int
     if (!(base >= 0.0 && base <= 1.0) || !(s_min > 0.0) || !(s_max >= s_min)) return DBMP_EINVAL;
     if (!(sigma_c >= 0.0) || ((uintptr_t)workspace & 15)) return DBMP_EINVAL;
     const long long npix = (long long)H * W;
-    const SaLayout L = sa_layout(npix, H, W);
+    const SaLayout L = sa_layout(H, W);
     if (workspace_bytes < (long long)L.total) return DBMP_EINVAL;
     char *ws = (char *)workspace;
     auto *minmax = (unsigned long long *)(ws + L.minmax);
