@@ -675,9 +675,11 @@ int dbmp_sa_init(dbmp_aids_stream stream, const float *target, int H, int W, int
     auto *gsum = (long long *)(ws + L.gsum);
     auto *bsum = (long long *)(ws + L.bsum);
     hipStream_t st = (hipStream_t)stream;
-    const int rows = lv_rows(H, W);
-    const dim3 lvg((W + LV_W - 1) / LV_W, (H + rows - 1) / rows);
-    launch_local_var(st, lvg, rows, target, H, W, win / 2, lv, bmm);
+    int lh = H, lw = W;
+    lv_shape(lh, lw);
+    const int rows = lv_rows(lh, lw);
+    const dim3 lvg((lw + LV_W - 1) / LV_W, (lh + rows - 1) / rows);
+    launch_local_var(st, lvg, rows, target, lh, lw, win / 2, lv, bmm);
     int nslots = (int)(lvg.x * lvg.y);
     if (nslots > 2048) {  // too many for every workgroup of k_nlv to read
         k_lv_minmax<<<1, 1024, 0, st>>>(bmm, nslots, minmax);

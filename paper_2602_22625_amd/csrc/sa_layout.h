@@ -26,12 +26,23 @@ inline int lv_rows(int H, int W)
     return wgs >= 512 ? 32 : 8;
 }
 
+// A single column lies in memory as a single row does, whose windows are the same: the local variance
+// takes it as one, 64 pixels per wave (65,536 x 1: 57 us for the start of a fit as a column, 31 as a row).
+inline void lv_shape(int &H, int &W)
+{
+    if (W == 1) {
+        W = H;
+        H = 1;
+    }
+}
+
 inline SaLayout sa_layout(int H, int W)
 {
+    lv_shape(H, W);
     const size_t npix = (size_t)H * W, nb = (npix + NLV_BLOCK - 1) / NLV_BLOCK;
     const size_t rows = (size_t)lv_rows(H, W);
     const size_t nblk = (((size_t)W + LV_W - 1) / LV_W) * (((size_t)H + rows - 1) / rows);
-    const size_t blocks16 = (((size_t)W + 15) / 16) * (((size_t)H + 15) / 16);
+    const size_t blocks16 = (((size_t)W + 15) / 16) * (((size_t)H + 15) / 16);  // (symmetric)
     auto up = [](size_t x, size_t a) { return (x + a - 1) / a * a; };
     const size_t total = 256 + up(16 * blocks16, 256) + 2 * up(8 * npix, 256) +
                          up(8 * ((npix + 2047) / 2048), 256);

@@ -16,6 +16,7 @@ void check(int H, int W)
     const size_t n = (size_t)H * W, nb = (n + 4095) / 4096;
     const size_t want = 256 + up256(16 * ((((size_t)W + 15) / 16) * (((size_t)H + 15) / 16))) +
                         2 * up256(8 * n) + up256(8 * ((n + 2047) / 2048));
+    dbmp::lv_shape(H, W);
     const size_t rows = (size_t)dbmp::lv_rows(H, W);
     const size_t nblk = (((size_t)W + 63) / 64) * (((size_t)H + rows - 1) / rows);
     const bool ok = L.total == want && L.used <= L.total && L.minmax == 0 && L.bmm >= 16 &&
