@@ -186,12 +186,12 @@ constexpr int stage_kb(int nch, int mt, int nt)
 {
     return stage_chunks(nch, mt, nt) * (nt + 4 * mt);
 }
-// Stages in LDS: as many as leave room for two workgroups per compute unit, at most five.
+// Stages in LDS: as many as leave room for two workgroups per compute unit, three to five. (Three of
+// the 32 KB stages of 1 x 4 tiles with 128 channels or more take 96 KB: one workgroup there.)
 constexpr int ring(int nch, int mt, int nt)
 {
     return std::max(3, std::min(5, 80 / stage_kb(nch, mt, nt)));
 }
-
 // Waits until at most N vector-memory operations of this wave are outstanding (and its LDS reads
 // are done), then for the workgroup. A __syncthreads() would wait for all of them.
 template <int N>
@@ -213,6 +213,9 @@ __device__ __forceinline__ void copy_to_lds(GChar *p, u16 *dst)
 }
 
 // C = 32 NCH channels of K per tap; dense layers: a.taps runs of C inputs per row.
+// (Four waves per SIMD bound the registers of the smallest tiles alone; where the stages' LDS allows
+// fewer, the compiler says so and takes what that allows. A bound of what it allows gave other code
+// and the same times.)
 template <int MODE, int NCH, int MT, int NT>
 __global__ void __launch_bounds__(256, 4) k_conv(ConvArgs a)
 {
