@@ -324,8 +324,8 @@ k_prep(const float *params, const int *__restrict__ idx, long long n_rows,
     // coalesced), then the waves take the 9 float64 exponentials and the sine and cosine item by
     // item, so that a wave runs either kind and three quarters of them need no sine and cosine
     // (dealt primitive by primitive, every wave ran both one after the other). With the records'
-    // coalesced stores and Adam's powers by squaring, a fit's binning went from 7.8 to 6.2 us (64
-    // primitives, latency), 9.8 to 8.9 (4,096) and 19.4 to 17.9 (65,536). The values are
+    // coalesced stores and Adam's powers by squaring, a fit's binning went from 8.0 to 6.4 us (64
+    // primitives, latency), 10.2 to 9.0 (4,096) and 18.9 to 17.5 (65,536). The values are
     // those of a one-lane evaluation; the update is k_adam's (zero_grad), bit for bit.
     // The record lane's image record, bitmap index and bitmap box, requested before the
     // parameter-wise passes so that their latency overlaps them.

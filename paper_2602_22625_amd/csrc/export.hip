@@ -285,9 +285,9 @@ struct LayerArgs {
 // many values as the bitmap texels: 64 neighbouring pixels read texels of some 40 cache lines, and
 // the L1 serves one line per clock, so four loads per value from memory cost about 160 clocks per
 // 64 values. Bound by instructions (82 % of the issue slots, 42 per value of which 14 in float64).
-// 54 million values at 1024 x 1024 x 2, 8,192 primitives, 64 x 64 float32 bitmaps: 271 us from
+// 54 million values at 1024 x 1024 x 2, 8,192 primitives, 64 x 64 float32 bitmaps: 276 us from
 // memory, 145 with comparisons in the loop over the copy (four values at a time or 512 threads
-// were no faster), 108 now; 217 MB are written, 43 us. Smaller boxes read from memory.
+// were no faster), 113 now; 217 MB are written, 43 us. Smaller boxes read from memory.
 // (A grid of (primitive, tile row, tile column) sized by the largest box launched mostly empty
 // workgroups: 5.1 ms at 2048 x 2048 with 65,536 primitives against 0.59 ms; one wave per primitive
 // took 1.17 ms: the largest boxes then run on 64 lanes.)

@@ -530,8 +530,9 @@ k_raster_fwd(const PrimRec *__restrict__ recs, int *__restrict__ lists, int list
         // What needs the tile's number alone is requested before the count is known: the image,
         // the target pixel and, in the pipelined build, whose few waves cannot hide a latency, the
         // list's first 64 entries (its capacity is a multiple of 32; those past the count are not
-        // used): with the one-wave sort, 22.3 -> 21.4 us at 512 x 512. Where waves hide it, the
-        // entries read in vain cost more (1,234 against 1,218 us per step of 64 uneven fits).
+        // used): with the one-wave sort, 26.6 -> 26.2 us by a launch's events at 512 x 512. Where waves
+        // hide it, the entries read in vain cost more (1,234 against 1,218 us per step of 64 uneven
+        // fits).
         int *seg = lists + (size_t)tile * list_cap;
         const bool spec = PIPE && threadIdx.x < 64 && (int)threadIdx.x < list_cap;
         const int entry = spec ? seg[threadIdx.x] : 0;
