@@ -26,13 +26,13 @@
 // stores after the class's last.
 //
 // Measured at batch 64 (forward, then input gradient; us, against the gather product before):
-//   256^2 x 8 -> 32    28 (68)             128^2 x 32 -> 64   30 (39), 43 (157)
-//   64^2 x 64 -> 128   21 (35), 23 (75)    32^2 x 128 -> 256  16 (32), 27 (60)
-//   16^2 x 256 -> 256  11 (39), 16 (38)    8^2 x 256 -> 256    6 (39),  7 (25)
+//   256^2 x 8 -> 32    30 (78)             128^2 x 32 -> 64   28 (44), 44 (160)
+//   64^2 x 64 -> 128   21 (38), 23 (76)    32^2 x 128 -> 256  15 (33), 21 (60)
+//   16^2 x 256 -> 256  12 (34), 15 (37)    8^2 x 256 -> 256    7 (34),  8 (25)
 // The first two move 134 and 100 MB (167 MB for the gradient): 26, 20 and 33 us at the rate of a
 // large copy, which bounds them; the others are bound by the latency of their stages.
-// Dense layers at 1,024 rows (64 images; 256 -> 512 and 512 -> 512, latency): forward 4.7 (8.5) and
-// 5.0 (11.6), input gradient 3.9 (9.6) and 4.7 (9.8).
+// Dense layers at 1,024 rows (64 images; 256 -> 512 and 512 -> 512, latency): forward 4.0 (7.4) and
+// 4.6 (9.5), input gradient 3.9 (9.3) and 4.7 (9.4).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -192,6 +192,7 @@ constexpr int ring(int nch, int mt, int nt)
 {
     return std::max(3, std::min(5, 80 / stage_kb(nch, mt, nt)));
 }
+
 // Waits until at most N vector-memory operations of this wave are outstanding (and its LDS reads
 // are done), then for the workgroup. A __syncthreads() would wait for all of them.
 template <int N>
