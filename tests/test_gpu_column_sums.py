@@ -57,7 +57,19 @@ def _us(M, N):
 
 
 def test_many_rows_are_read_fast():
-    """1,048,576 x 264 (554 MB): 90 us, 129 with a workgroup per compute unit. The line is at 110."""
+    """1,048,576 x 264 (554 MB) against a copy of them, which reads and writes as much: 90 us of about 210, 129
+    with a workgroup per compute unit. The line is at half."""
     us = _us(1 << 20, 264)
-    print("%.1f us" % us)
-    assert us < 110
+    a = torch.empty(1 << 20, 264, device="cuda", dtype=torch.bfloat16)
+    b = torch.empty_like(a)
+    t = []
+    for _ in range(15):
+        e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        e[0].record()
+        for _ in range(5):
+            b.copy_(a)
+        e[1].record()
+        e[1].synchronize()
+        t.append(e[0].elapsed_time(e[1]) * 200)
+    print("sums %.1f us, copy %.1f us" % (us, min(t)))
+    assert us < 0.5 * min(t)
